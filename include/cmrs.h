@@ -474,8 +474,10 @@ cmrs_status_t cmrs_validate_csr(int32_t rows, int32_t cols, int32_t nnz, const i
  * cmrs_mlp_forward:  H1, H2 (batch x 64) and Y (batch x 24).
  * cmrs_mlp_backward: from dY (batch x 24) and the forward activations, the
  *   parameter gradients `grads` (CMRS_SEL_PARAMS) with scratch dH2, dH1
- *   (batch x 64 each); batch sums in sample order (deterministic).
+ *   (batch x 64 each); the batch is summed in a fixed order (deterministic).
  * cmrs_mse_grad:     dY = scale * (Y - T), n values.
+ * cmrs_mlp_grads:    forward, dY = scale * (Y - T) and backward in one call:
+ *   the same values as the three calls above, in two launches; batch >= 1.
  * cmrs_adam_step:    one Adam update of n parameters (step >= 1 for the bias
  *   corrections).
  * All arrays are caller-owned device fp32 arrays.  Errors: CMRS_ERR_INVALID_VALUE
@@ -495,6 +497,9 @@ cmrs_status_t cmrs_mlp_forward(int32_t batch, const float *X, const float *param
 cmrs_status_t cmrs_mlp_backward(int32_t batch, const float *X, const float *params, const float *H1,
                                 const float *H2, const float *dY, float *dH2, float *dH1, float *grads,
                                 hipStream_t stream);
+cmrs_status_t cmrs_mlp_grads(int32_t batch, const float *X, const float *T, const float *params, float scale,
+                             float *H1, float *H2, float *Y, float *dY, float *dH2, float *dH1, float *grads,
+                             hipStream_t stream);
 cmrs_status_t cmrs_mse_grad(int32_t n, const float *Y, const float *T, float *dY, float scale, hipStream_t stream);
 cmrs_status_t cmrs_adam_step(int32_t n, float *params, const float *grads, float *m, float *v, float lr, float beta1,
                              float beta2, float eps, int32_t step, hipStream_t stream);

@@ -126,6 +126,8 @@ lib.cmrs_mlp_forward.argtypes = [_i32, _vp, _vp, _vp, _vp, _vp, _vp]
 lib.cmrs_mlp_forward.restype = ctypes.c_int
 lib.cmrs_mlp_backward.argtypes = [_i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
 lib.cmrs_mlp_backward.restype = ctypes.c_int
+lib.cmrs_mlp_grads.argtypes = [_i32, _vp, _vp, _vp, ctypes.c_float] + [_vp] * 8
+lib.cmrs_mlp_grads.restype = ctypes.c_int
 lib.cmrs_mse_grad.argtypes = [_i32, _vp, _vp, _vp, ctypes.c_float, _vp]
 lib.cmrs_mse_grad.restype = ctypes.c_int
 lib.cmrs_adam_step.argtypes = [_i32, _vp, _vp, _vp, _vp] + [ctypes.c_float] * 4 + [_i32, _vp]
@@ -143,6 +145,7 @@ EXPORTED = ["cmrs_abi_version", "cmrs_num_strips", "cmrs_bits_for_height", "cmrs
             "cmrs_padded_bits", "cmrs_padded_plan_workspace", "cmrs_padded_plan", "cmrs_padded_from_csr",
             "cmrs_padded_spmv",
             "cmrs_calib_stream_read", "cmrs_calib_gather", "cmrs_features", "cmrs_mlp_forward", "cmrs_mlp_backward",
+            "cmrs_mlp_grads",
             "cmrs_mse_grad", "cmrs_adam_step", "cmrs_status_string", "cmrs_last_error"]
 
 

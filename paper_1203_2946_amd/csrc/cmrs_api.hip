@@ -621,6 +621,17 @@ cmrs_status_t cmrs_mlp_backward(int32_t batch, const float* X, const float* para
                     "cmrs_mlp_backward");
 }
 
+cmrs_status_t cmrs_mlp_grads(int32_t batch, const float* X, const float* T, const float* params, float scale,
+                             float* H1, float* H2, float* Y, float* dY, float* dH2, float* dH1, float* grads,
+                             hipStream_t stream) {
+    g_last_error[0] = 0;
+    if (batch <= 0) return fail(CMRS_ERR_INVALID_VALUE, "batch must be positive");
+    if (!X || !T || !params || !H1 || !H2 || !Y || !dY || !dH2 || !dH1 || !grads)
+        return fail(CMRS_ERR_INVALID_VALUE, "NULL pointer");
+    return from_hip(cmrs::launch_mlp_grads(batch, X, T, params, scale, H1, H2, Y, dY, dH2, dH1, grads, stream),
+                    "cmrs_mlp_grads");
+}
+
 cmrs_status_t cmrs_mse_grad(int32_t n, const float* Y, const float* T, float* dY, float scale, hipStream_t stream) {
     g_last_error[0] = 0;
     if (n < 0) return fail(CMRS_ERR_INVALID_VALUE, "negative size");

@@ -86,6 +86,9 @@ hipError_t launch_mlp_forward(int batch, const float* X, const float* params, fl
                               hipStream_t stream);
 hipError_t launch_mlp_backward(int batch, const float* X, const float* params, const float* H1, const float* H2,
                                const float* dY, float* dH2, float* dH1, float* grads, hipStream_t stream);
+hipError_t launch_mlp_grads(int batch, const float* X, const float* T, const float* params, float scale, float* H1,
+                            float* H2, float* Y, float* dY, float* dH2, float* dH1, float* grads,
+                            hipStream_t stream);
 hipError_t launch_mse_grad(int n, const float* Y, const float* T, float* dY, float scale, hipStream_t stream);
 hipError_t launch_adam(int n, float* p, const float* g, float* m, float* v, float lr, float b1, float b2, float eps,
                        int step, hipStream_t stream);

@@ -91,14 +91,13 @@ class Mlp:
     def grads(self, X: torch.Tensor, T: torch.Tensor):
         """Parameter gradients of mean((Y - T)^2) over all batch x class entries."""
         b = X.shape[0]
-        H1, H2, Y = self.forward(X)
-        dY = torch.empty_like(Y)
-        cmrs._check(_L.cmrs_mse_grad(Y.numel(), _p(Y), _p(T), _p(dY), 2.0 / Y.numel(), _s()), "cmrs_mse_grad")
-        dH2 = torch.empty_like(H2)
-        dH1 = torch.empty_like(H1)
+        Y = torch.empty(b, N_CLASSES, device=X.device)
         g = torch.empty_like(self.params)
-        cmrs._check(_L.cmrs_mlp_backward(b, _p(X), _p(self.params), _p(H1), _p(H2), _p(dY), _p(dH2), _p(dH1), _p(g),
-                                         _s()), "cmrs_mlp_backward")
+        # Activations and their gradients (H1, H2, dH1, dH2, dY) live for the call only.
+        ws = torch.empty(b * (4 * HIDDEN + N_CLASSES), device=X.device)
+        h, n = _p(ws), 4 * HIDDEN * b
+        cmrs._check(_L.cmrs_mlp_grads(b, _p(X), _p(T), _p(self.params), 2.0 / Y.numel(), h, h + n, _p(Y), h + 4 * n,
+                                      h + 2 * n, h + 3 * n, _p(g), _s()), "cmrs_mlp_grads")
         return Y, g
 
     def train(self, X: torch.Tensor, T: torch.Tensor, steps: int = 4000, lr: float = 2e-3, log_every: int = 0):

@@ -37,6 +37,8 @@
 // workspace beyond that.
 #include <limits.h>
 
+#include <type_traits>
+
 #include "cmrs_device.hpp"
 #include "cmrs_internal.hpp"
 
@@ -91,8 +93,8 @@ __device__ inline int pow2_at_least(int n) {
 
 // Ascending bitonic network over keys k[0..P), P a power of two, run by
 // `nthreads` threads numbered `tid`; `sync` orders the passes.
-template <typename Sync>
-__device__ inline void bitonic_sort(uint64_t* k, int P, int tid, int nthreads, Sync sync) {
+template <typename Key, typename Sync>
+__device__ inline void bitonic_sort(Key* k, int P, int tid, int nthreads, Sync sync) {
     for (int size = 2; size <= P; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
             for (int t = tid; t < P / 2; t += nthreads) {
@@ -112,6 +114,26 @@ __device__ inline void bitonic_sort(uint64_t* k, int P, int tid, int nthreads, S
 
 // ------------------------------------------------------------------ whole-wave paths
 
+// Pointers into LDS.  Functions that are not inlined take their LDS this way:
+// with a generic pointer their accesses are flat ones, which are slower, and
+// whose address before the instruction's own offset has to lie in the LDS
+// aperture, which an index with a negative part need not keep.
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+typedef __attribute__((address_space(3))) uint64_t LdsKey;
+typedef __attribute__((address_space(3))) int LdsInt;
+
+// The word at an LDS address: a signed number, so that one word before the
+// first stays below it.
+__device__ inline int lds_address(const LdsWord* p) { return static_cast<int>(reinterpret_cast<uintptr_t>(p)); }
+__device__ inline uint32_t lds_word(int address) { return *reinterpret_cast<const LdsWord*>(static_cast<uintptr_t>(address)); }
+
+// Largest value of v over the wave.
+__device__ inline int wave_max(int v) {
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
+    return uniform(v);
+}
+
 // Merge of the row runs of strips held in registers, G lanes per strip, slot u
 // of lane q holding entry q + G*u: words (col << bits | RowInStrip) in wd and
 // their current place in the strip in pos.  LDS
@@ -120,42 +142,82 @@ __device__ inline void bitonic_sort(uint64_t* k, int P, int tid, int nthreads, S
 // different runs never tie (their RowInStrip fields differ), so
 // an entry's place after a level is its rank in its own run plus the number
 // of partner-run words below it.  On return pos holds each entry's place in
-// the sorted strip.  The caller has made A and rt visible to the wave.
-template <int HB, int G, int E>
-__device__ inline void merge_runs_regs(uint32_t* A, uint32_t* B, const int* rt, const uint32_t (&wd)[E],
-                                       int (&pos)[E], int umax, bool go, int n, int q) {
-#pragma unroll 1
+// the sorted strip.  The caller has made A and rt visible to the wave; row_max
+// bounds the rows' lengths and n_max the strips' (both uniform, n_max <= G*E).
+//
+// Bound by VALU issue: with a search loop per entry the sorted conversion of
+// 2^20 Poisson(16) rows at height 8 issued VALU instructions on 99 % of its
+// 154 us, 363 of them per 64 entries.  So the search is a fixed number of
+// steps for the whole wave, four instructions each, on LDS addresses: cur is
+// the last word known to be below the entry's own (one before the run at
+// first), and a step moves it on by a power of two where that stays in the
+// run and below.  A step may read past its run: up to 4 kWave E bytes past B,
+// which the buffer holds behind the last wave's slice (merge_pad).  Conversions
+// (fp64, us): 2^20 Poisson(16) rows at height 8 150 -> 131, at height 16 184 ->
+// 141; 27-point stencil of 10^6 rows at height 8 233 -> 178; 5-point stencil in
+// bf16 at height 32 70 -> 49.
+template <int HB, int G, int E, bool EXACT>
+__device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt, const uint32_t (&wd)[E],
+                                       int (&pos)[E], int umax, bool go, int n, int q, int row_max, int n_max) {
+#pragma unroll
     for (int k = 0; (1 << k) < HB; ++k) {
         if (k > 0) wave_lds_sync();
+        const int longest = min(row_max << k, n_max);
+        const int top = longest > 0 ? 4 << (31 - __clz(longest)) : 0;
+        const int first = lds_address(A) - 4;
+        // Level k of the slots u0 .. u0 + C - 1, their searches in step.
+        const auto level = [&](auto count, int u0) {
+            constexpr int C = decltype(count)::value;
+            int start[C], cur[C], last[C];
 #pragma unroll
-        for (int u = 0; u < E; ++u) {
-            if (u >= umax) break;
-            const int run = static_cast<int>(wd[u] & static_cast<uint32_t>(HB - 1)) >> k;
-            const int partner = run ^ 1;
-            const int run_lo = rt[run << k];
-            const int merged_lo = rt[(run & ~1) << k];
-            const int p_lo = rt[partner << k];
-            const int p_hi = rt[(partner + 1) << k];
-            if (go && q + G * u < n) {
-                int a = p_lo, len = p_hi - p_lo;
-                while (len > 0) {
-                    const int half = len >> 1;
-                    if (A[a + half] < wd[u]) {
-                        a += half + 1;
-                        len -= half + 1;
-                    } else {
-                        len = half;
-                    }
-                }
-                pos[u] = merged_lo + (pos[u] - run_lo) + (a - p_lo);
-                B[pos[u]] = wd[u];
+            for (int v = 0; v < C; ++v) {
+                const int partner = (static_cast<int>(wd[u0 + v]) & (HB - 1) & -(1 << k)) ^ (1 << k);
+                start[v] = cur[v] = first + 4 * rt[partner];
+                last[v] = first + 4 * rt[partner + (1 << k)];
             }
+            for (int step = top; step > 3; step >>= 1) {
+                uint32_t x[C];
+#pragma unroll
+                for (int v = 0; v < C; ++v) x[v] = lds_word(cur[v] + step);
+#pragma unroll
+                for (int v = 0; v < C; ++v) {
+                    const int t = cur[v] + step;
+                    cur[v] = static_cast<int>(t <= last[v]) & static_cast<int>(x[v] < wd[u0 + v]) ? t : cur[v];
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < C; ++v) {
+                const int u = u0 + v;
+                // The partner's words in front of a left run's entry move it
+                // back; a right run's entry already stands behind all of them.
+                const bool right = (wd[u] >> k) & 1u;
+                pos[u] += (cur[v] - (right ? last[v] : start[v])) >> 2;
+                if ((2 << k) < HB && go && q + G * u < n) B[pos[u]] = wd[u];
+            }
+        };
+        // Four slots at a time; what is left of them with EXACT by a set of its
+        // own size (an empty slot costs as much as a full one), without as four.
+#pragma unroll
+        for (int u0 = 0; u0 < E; u0 += 4) {
+            const int left = umax - u0;
+            if (left <= 0) break;
+            if (!EXACT || left >= 4)
+                level(std::integral_constant<int, 4>(), u0);
+            else if (left == 3)
+                level(std::integral_constant<int, 3>(), u0);
+            else if (left == 2)
+                level(std::integral_constant<int, 2>(), u0);
+            else
+                level(std::integral_constant<int, 1>(), u0);
         }
-        uint32_t* tmp = A;
+        LdsWord* tmp = A;
         A = B;
         B = tmp;
     }
 }
+
+// 64-bit words a search may read past the last wave's slice of kWave*E.
+constexpr int merge_pad(int E) { return kWave * E / 2; }
 
 // Sorted conversion of one strip of at most kWave*E entries by the whole wave,
 // words in registers (slot u of lane l: entry l + kWave*u), in its LDS slice
@@ -165,14 +227,14 @@ __device__ inline void merge_runs_regs(uint32_t* A, uint32_t* B, const int* rt, 
 template <int HB, int E, typename ET>
 __device__ inline void sort_strip_mid(int strip, int rows, int height, int bits, const int* __restrict__ row_ptr,
                                       const int* __restrict__ col_ind, const ET* __restrict__ val_in,
-                                      uint32_t* __restrict__ col_word, ET* __restrict__ val_out, uint64_t* slice,
-                                      int* rt, int lane) {
+                                      uint32_t* __restrict__ col_word, ET* __restrict__ val_out, LdsKey* slice,
+                                      LdsInt* rt, int lane) {
     const StripRows sr = load_strip_rows(strip, rows, height, row_ptr, lane);
     const int n = sr.s1 - sr.s0;
     const int umax = uniform((n + kWave - 1) / kWave);
     const uint32_t mask = (1u << bits) - 1u;
-    uint32_t* A = reinterpret_cast<uint32_t*>(slice);
-    uint32_t* B = A + kWave * E;
+    LdsWord* A = reinterpret_cast<LdsWord*>(slice);
+    LdsWord* B = A + kWave * E;
     uint32_t wd[E];
     int pos[E];
 #pragma unroll
@@ -201,7 +263,9 @@ __device__ inline void sort_strip_mid(int strip, int rows, int height, int bits,
         }
     }
     if (ballot(bad) == 0ull) {
-        merge_runs_regs<HB, kWave, E>(A, B, rt, wd, pos, umax, true, n, lane);
+        const int next_row = __shfl_down(sr.myrp, 1);
+        const int row_max = wave_max(lane < sr.nr ? next_row - sr.myrp : 0);
+        merge_runs_regs<HB, kWave, E, false>(A, B, rt, wd, pos, umax, true, n, lane, row_max, n);
 #pragma unroll
         for (int u = 0; u < E; ++u) {
             if (u >= umax) break;
@@ -272,10 +336,11 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
     static_assert(G >= HB && G <= kWave && G >= 2, "group width");
     constexpr int NG = kWave / G;
     constexpr int CAP = G * E;
-    __shared__ uint64_t lds[kConvWaves][kWave * E];
+    __shared__ uint64_t lds[kConvWaves * kWave * E + merge_pad(E)];
     __shared__ int rowtab[kConvWaves][NG * (HB + 1)];
     const int lane = lane_id();
     const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
+    LdsKey* const slice = (LdsKey*)lds + wave * kWave * E;
     const int strip0 = (xcd_logical_block(blockIdx.x, gridDim.x) * kConvWaves + wave) * NG;
     if (strip0 >= strips) return;
     const int g = lane / G, q = lane % G, gbase = g * G;
@@ -317,9 +382,9 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
         // Words of every strip the group holds in LDS by place, and the
         // strip-relative row pointers of rows 0..HB (rows past the strip: n).
         const bool fits = valid && !special;
-        uint32_t* A = reinterpret_cast<uint32_t*>(&lds[wave][0]) + gbase * E;
-        uint32_t* B = reinterpret_cast<uint32_t*>(&lds[wave][0]) + kWave * E + gbase * E;
-        int* rtab = &rowtab[wave][g * (HB + 1)];
+        LdsWord* A = reinterpret_cast<LdsWord*>(slice) + gbase * E;
+        LdsWord* B = A + kWave * E;
+        LdsInt* rtab = (LdsInt*)&rowtab[wave][g * (HB + 1)];
         uint32_t wd[E];
         int pos[E];
 #pragma unroll
@@ -357,7 +422,10 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
                 ws_big[atomicAdd(&ws_count[1], 1)] = strip;
         }
         const bool go = valid && !special;
-        merge_runs_regs<HB, G, E>(A, B, rtab, wd, pos, umax, go, n, q);
+        const int next_row = __shfl_down(myrp, 1);
+        const int row_end = q + 1 < nr ? next_row : s1;
+        const int row_max = HB > 1 ? wave_max(go && q < nr ? row_end - myrp : 0) : 0;
+        merge_runs_regs<HB, G, E, true>(A, B, rtab, wd, pos, umax, go, n, q, row_max, umax * G);
         // Out from registers: each entry to its place in the sorted strip.
         // (Staging through LDS as the tall-strip kernel does was measured
         // slower here: 133 -> 137 us at height 2, 156 -> 164 us at height 4.)
@@ -375,7 +443,7 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
             const int leader = __ffsll(static_cast<unsigned long long>(mids)) - 1;
             mids &= mids - 1;
             sort_strip_mid<HB, E, ET>(strip0 + leader / G, rows, height, bits, row_ptr, col_ind, val_in, col_word,
-                                      val_out, lds[wave], rowtab[wave], lane);
+                                      val_out, slice, (LdsInt*)rowtab[wave], lane);
         }
     }
 }
@@ -1303,7 +1371,7 @@ __global__ __launch_bounds__(kBlockSortThreads) void sort_lists_kernel(
     uint64_t* __restrict__ gkeys) {
     constexpr int NW = kBlockSortThreads / kWave;
     static_assert(kBlockSortCap >= NW * kWaveSortCap, "a short strip's keys per wave");
-    __shared__ uint64_t skeys[kBlockSortCap];
+    __shared__ uint64_t skeys[kBlockSortCap + merge_pad(kWaveSortCap / kWave)];
     __shared__ int rt[HB + 1];
     __shared__ int taken[2];
     __shared__ int wrt[NW][HB + 1];
@@ -1350,11 +1418,11 @@ __global__ __launch_bounds__(kBlockSortThreads) void sort_lists_kernel(
         }
     }
     const int scount = ws_count[0];
-    uint64_t* slice = skeys + wave * kWaveSortCap;
+    LdsKey* slice = (LdsKey*)skeys + wave * kWaveSortCap;
     const int nwaves = static_cast<int>(gridDim.x) * NW;
     for (int it = static_cast<int>(blockIdx.x) * NW + wave; it < scount; it += nwaves)
         sort_strip_mid<HB, kWaveSortCap / kWave, ET>(ws_small[it], rows, height, bits, row_ptr, col_ind, val_in,
-                                                     col_word, val_out, slice, wrt[wave], lane);
+                                                     col_word, val_out, slice, (LdsInt*)wrt[wave], lane);
 }
 
 __global__ void validate_csr_kernel(int rows, int cols, int nnz, const int* __restrict__ row_ptr,

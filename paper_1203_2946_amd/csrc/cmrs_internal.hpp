@@ -25,10 +25,10 @@ inline size_t dtype_bytes(cmrs_dtype_t t) {
 }
 
 // Strips that one wave sorts in its LDS slice (sorted conversion), and the
-// largest strip a 1024-thread workgroup sorts in LDS; longer strips are
-// sorted in the global workspace.
+// largest strip a 512-thread workgroup merges or sorts in LDS; longer strips
+// are streamed or sorted in the global workspace.
 constexpr int kWaveSortCap = 1024;
-constexpr int kBlockSortCap = 16384;
+constexpr int kBlockSortCap = 8192;
 
 struct FromCsrWorkspaceLayout {
     size_t small_off;   // int32 counts at offset 0 (short / long list), short-strip list at small_off

@@ -28,13 +28,13 @@
 // levels, in LDS: each entry counts the keys of the partner run below its own
 // (binary search) and moves to its place in the merged run.  Keys are
 // (word << 32 | position in strip), unique, so the result is the stable order.
-// Strips that are longer than a group holds, or whose rows are not sorted,
-// go to a list in the workspace: strips of up to 1024 entries are sorted by
-// one wave (run merge, or a bitonic network for unsorted rows); longer ones
-// by a 1024-thread workgroup, in LDS up to 16384 entries (each entry ranked
-// against the strip's short rows gathered and sorted once, and by a binary
-// search over each long row; a bitonic network for unsorted rows), in the
-// workspace beyond that.
+// Matrices of longer strips (a mean of 450 to 3800 entries) give each strip to a
+// workgroup, which merges the same way.  Strips that are longer than that, or
+// whose rows are not sorted, go to a list in the workspace: strips of up to 1024
+// entries are sorted by one wave (run merge, or a bitonic network for unsorted
+// rows); of longer ones, one long row among short ones is streamed against the
+// short rows' sorted words, others are merged by a workgroup in LDS up to 8192
+// entries, in the workspace beyond that, unsorted rows by a bitonic network.
 #include <limits.h>
 
 #include <type_traits>
@@ -46,9 +46,10 @@ namespace cmrs {
 
 constexpr int kConvWaves = 4;
 constexpr int kConvThreads = kConvWaves * kWave;
-constexpr int kBlockSortThreads = 1024;
-// Workgroups of the long-strip sort: its LDS allows one per CU, 256 CUs.
-constexpr int kBlockSortGrid = 256;
+constexpr int kBlockSortThreads = 512;
+// Workgroups of the listed-strip sort: its LDS and registers allow two per
+// CU, 256 CUs.
+constexpr int kBlockSortGrid = 512;
 
 __global__ void set_ints_kernel(int32_t* p, int32_t n, int32_t v) {
     if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < n) p[threadIdx.x] = v;
@@ -92,24 +93,28 @@ __device__ inline int pow2_at_least(int n) {
 }
 
 // Ascending bitonic network over keys k[0..P), P a power of two, run by
-// `nthreads` threads numbered `tid`; `sync` orders the passes.
+// `nthreads` threads numbered `tid`; `sync` orders the passes.  The keys are
+// elements base .. base + P of a larger network's: bitonic_merge runs the
+// passes of one size from stride `from` down.
 template <typename Key, typename Sync>
-__device__ inline void bitonic_sort(Key* k, int P, int tid, int nthreads, Sync sync) {
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = tid; t < P / 2; t += nthreads) {
-                const int i = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
-                const int l = i + stride;
-                const bool up = (i & size) == 0;
-                const uint64_t a = k[i], b = k[l];
-                if ((a > b) == up) {
-                    k[i] = b;
-                    k[l] = a;
-                }
+__device__ inline void bitonic_merge(Key* k, int P, int size, int from, int base, int tid, int nthreads, Sync sync) {
+    for (int stride = from; stride > 0; stride >>= 1) {
+        for (int t = tid; t < P / 2; t += nthreads) {
+            const int i = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
+            const int l = i + stride;
+            const bool up = ((base + i) & size) == 0;
+            const uint64_t a = k[i], b = k[l];
+            if ((a > b) == up) {
+                k[i] = b;
+                k[l] = a;
             }
-            sync();
         }
+        sync();
     }
+}
+template <typename Key, typename Sync>
+__device__ inline void bitonic_sort(Key* k, int P, int base, int tid, int nthreads, Sync sync) {
+    for (int size = 2; size <= P; size <<= 1) bitonic_merge(k, P, size, size >> 1, base, tid, nthreads, sync);
 }
 
 // ------------------------------------------------------------------ whole-wave paths
@@ -138,7 +143,8 @@ __device__ inline int wave_max(int v) {
 // of lane q holding entry q + G*u: words (col << bits | RowInStrip) in wd and
 // their current place in the strip in pos.  LDS
 // buffers A and B (the group's words by place, A filled on entry) alternate
-// per level, level k merging the runs of 2^k rows pairwise; the words of
+// per level, level k merging the runs of 2^k rows pairwise (ONE: every level
+// leaves its words in A, the last one too, so that A ends sorted); the words of
 // different runs never tie (their RowInStrip fields differ), so
 // an entry's place after a level is its rank in its own run plus the number
 // of partner-run words below it.  On return pos holds each entry's place in
@@ -152,16 +158,17 @@ __device__ inline int wave_max(int v) {
 // the last word known to be below the entry's own (one before the run at
 // first), and a step moves it on by a power of two where that stays in the
 // run and below.  A step may read past its run: up to 4 kWave E bytes past B,
-// which the buffer holds behind the last wave's slice (merge_pad).  Conversions
+// which the buffer holds behind the last wave's slice (merge_pad); with CLAMP it
+// reads no further than one word before A.  sync orders the levels.  Conversions
 // (fp64, us): 2^20 Poisson(16) rows at height 8 150 -> 131, at height 16 184 ->
 // 141; 27-point stencil of 10^6 rows at height 8 233 -> 178; 5-point stencil in
 // bf16 at height 32 70 -> 49.
-template <int HB, int G, int E, bool EXACT>
+template <int HB, int G, int E, bool MAIN, bool ONE = false, bool CLAMP = false, typename Sync>
 __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt, const uint32_t (&wd)[E],
-                                       int (&pos)[E], int umax, bool go, int n, int q, int row_max, int n_max) {
-#pragma unroll
-    for (int k = 0; (1 << k) < HB; ++k) {
-        if (k > 0) wave_lds_sync();
+                                       int (&pos)[E], int umax, bool go, int n, int q, int row_max, int n_max,
+                                       Sync sync) {
+    const auto merge_level = [&](int k) {
+        if (k > 0) sync();
         const int longest = min(row_max << k, n_max);
         const int top = longest > 0 ? 4 << (31 - __clz(longest)) : 0;
         const int first = lds_address(A) - 4;
@@ -178,7 +185,7 @@ __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt,
             for (int step = top; step > 3; step >>= 1) {
                 uint32_t x[C];
 #pragma unroll
-                for (int v = 0; v < C; ++v) x[v] = lds_word(cur[v] + step);
+                for (int v = 0; v < C; ++v) x[v] = lds_word(CLAMP ? min(cur[v] + step, last[v]) : cur[v] + step);
 #pragma unroll
                 for (int v = 0; v < C; ++v) {
                     const int t = cur[v] + step;
@@ -192,16 +199,16 @@ __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt,
                 // back; a right run's entry already stands behind all of them.
                 const bool right = (wd[u] >> k) & 1u;
                 pos[u] += (cur[v] - (right ? last[v] : start[v])) >> 2;
-                if ((2 << k) < HB && go && q + G * u < n) B[pos[u]] = wd[u];
+                if (!ONE && (2 << k) < HB && go && q + G * u < n) B[pos[u]] = wd[u];
             }
         };
-        // Four slots at a time; what is left of them with EXACT by a set of its
-        // own size (an empty slot costs as much as a full one), without as four.
+        // Four slots at a time; what is left of them in the main kernel by a set
+        // of its own size (an empty slot costs as much as a full one).
 #pragma unroll
         for (int u0 = 0; u0 < E; u0 += 4) {
             const int left = umax - u0;
             if (left <= 0) break;
-            if (!EXACT || left >= 4)
+            if (!MAIN || left >= 4)
                 level(std::integral_constant<int, 4>(), u0);
             else if (left == 3)
                 level(std::integral_constant<int, 3>(), u0);
@@ -210,11 +217,28 @@ __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt,
             else
                 level(std::integral_constant<int, 1>(), u0);
         }
-        LdsWord* tmp = A;
-        A = B;
-        B = tmp;
+        if constexpr (ONE) {
+            sync();
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if (go && q + G * u < n) A[pos[u]] = wd[u];
+        } else {
+            LdsWord* tmp = A;
+            A = B;
+            B = tmp;
+        }
+    };
+    // The listed strips' kernel runs a level's code a few times per wave only,
+    // so there the levels share it: unrolled, it was mostly instruction fetch.
+    if constexpr (MAIN) {
+#pragma unroll
+        for (int k = 0; (1 << k) < HB; ++k) merge_level(k);
+    } else {
+#pragma unroll 1
+        for (int k = 0; (1 << k) < HB; ++k) merge_level(k);
     }
 }
+
 
 // 64-bit words a search may read past the last wave's slice of kWave*E.
 constexpr int merge_pad(int E) { return kWave * E / 2; }
@@ -265,7 +289,8 @@ __device__ inline void sort_strip_mid(int strip, int rows, int height, int bits,
     if (ballot(bad) == 0ull) {
         const int next_row = __shfl_down(sr.myrp, 1);
         const int row_max = wave_max(lane < sr.nr ? next_row - sr.myrp : 0);
-        merge_runs_regs<HB, kWave, E, false>(A, B, rt, wd, pos, umax, true, n, lane, row_max, n);
+        merge_runs_regs<HB, kWave, E, false>(A, B, rt, wd, pos, umax, true, n, lane, row_max, n,
+                                                 [] { wave_lds_sync(); });
 #pragma unroll
         for (int u = 0; u < E; ++u) {
             if (u >= umax) break;
@@ -287,7 +312,7 @@ __device__ inline void sort_strip_mid(int strip, int rows, int height, int bits,
                 slice[i] = ~0ull;
         }
         wave_lds_sync();
-        bitonic_sort(slice, P, lane, kWave, [] { wave_lds_sync(); });
+        bitonic_sort(slice, P, 0, lane, kWave, [] { wave_lds_sync(); });
         for (int i = lane; i < n; i += kWave) {
             const uint64_t kk = slice[i];
             col_word[sr.s0 + i] = static_cast<uint32_t>(kk >> 32);
@@ -425,7 +450,8 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
         const int next_row = __shfl_down(myrp, 1);
         const int row_end = q + 1 < nr ? next_row : s1;
         const int row_max = HB > 1 ? wave_max(go && q < nr ? row_end - myrp : 0) : 0;
-        merge_runs_regs<HB, G, E, true>(A, B, rtab, wd, pos, umax, go, n, q, row_max, umax * G);
+        merge_runs_regs<HB, G, E, true>(A, B, rtab, wd, pos, umax, go, n, q, row_max, umax * G,
+                                         [] { wave_lds_sync(); });
         // Out from registers: each entry to its place in the sorted strip.
         // (Staging through LDS as the tall-strip kernel does was measured
         // slower here: 133 -> 137 us at height 2, 156 -> 164 us at height 4.)
@@ -450,193 +476,258 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
 
 // ------------------------------------------------------------------ tall strips
 
-// Sorted CSR -> CMRS for tall strips, one wave per strip of at most
-// kWave*E entries (longer strips go to the workspace lists).  The merge of
-// the group kernel costs log2(height) levels of binary searches; here an
-// entry's place comes from one bucketing pass instead, whatever the height:
-// entries fall into NB buckets of about equal width over the strip's column
-// range [cmin, cmax] (NB about n/4; the bucket is a multiply and a shift of
-// c - cmin, non-decreasing in c), a count per bucket (LDS atomics) and a
-// scan give each bucket's start, the
-// keys (word << 32 | position in strip) are scattered by bucket, and an
-// entry's place is its bucket's start plus the number of keys of its bucket
-// below its own.  Keys are unique and ordered as the reorder of Sec. 4
-// requires (column, then RowInStrip, then CSR order), so unsorted rows and
-// duplicates need no special path.  A strip whose largest bucket holds more
-// than kBucketMax keys (columns bunched at a few values far apart) is sorted
-// by a bitonic network over the same keys instead.
-constexpr int kBucketMax = 64;
-// The sorted conversion uses it from this height (next power of two) on, for
-// strips of at least kBucketMinMean entries on average: one wave per strip
-// costs more than the merge for short strips (measured).
-constexpr int kBucketMinHeight = 16;
-constexpr double kBucketMinMean = 320.0;
+// The key (word << 32 | place) of entry i of a strip; all lanes of the wave
+// must be active.
+template <int HB>
+__device__ inline uint64_t strip_key(const StripRows& sr, int n, int i, int bits, const int* __restrict__ col_ind) {
+    const int r = row_in_strip<HB>(sr.myrp, sr.s0 + i, 0);
+    if (i >= n) return ~0ull;
+    const uint32_t w = (static_cast<uint32_t>(col_ind[sr.s0 + i]) << bits) | static_cast<uint32_t>(r);
+    return (static_cast<uint64_t>(w) << 32) | static_cast<uint32_t>(i);
+}
 
-template <int HB, int E, typename ET>
-__global__ __launch_bounds__(kConvThreads) void from_csr_bucket_kernel(
+template <typename Key, typename ET>
+__device__ inline void write_sorted_keys(const Key* K, const StripRows& sr, int n, const ET* __restrict__ val_in,
+                                         uint32_t* __restrict__ col_word, ET* __restrict__ val_out, int tid, int NT) {
+    for (int i = tid; i < n; i += NT) {
+        const uint64_t k = K[i];
+        col_word[sr.s0 + i] = static_cast<uint32_t>(k >> 32);
+        val_out[sr.s0 + i] = val_in[sr.s0 + static_cast<int>(static_cast<uint32_t>(k))];
+    }
+}
+
+// Sorted CSR -> CMRS for strips of several hundred to a few thousand entries, one
+// workgroup of NT threads per strip of at most 8 NT entries (longer strips go to
+// the workspace lists), words, values and places in registers.
+//
+// Rows sorted by column: a merge of the row runs (merge_runs_regs) in one LDS
+// buffer, which then holds the sorted words; the values go through the same LDS.
+// Both leave in order: a scatter into the strip's range would leave partly
+// written lines (each reaching HBM more than once).  Bound by VALU issue like the
+// group kernel, with six waves per SIMD (eight spilled registers: 188 us against
+// 157 on 2^20 Poisson(16) rows, fp64, height 32; one wave per strip with 20
+// entries per lane had four: 249 us).  Strips like these went to the lists or,
+// bunched columns at height 16 and up, through the bitonic network: band of 129,
+// fp32, height 8/16/32 1068/3252/3313 -> 212/282/456 us; 27-point stencil, fp64,
+// height 32 640 -> 284 us; Poisson(48) rows, fp64, height 32 3840 -> 231 us.
+//
+// Rows not sorted: one bucketing pass, whatever the height: entries fall into NB
+// buckets of about equal width over the strip's column range [cmin, cmax] (NB
+// about n/4; the bucket is a multiply and a shift of c - cmin, non-decreasing in
+// c), a count per bucket (LDS atomics) and a scan give each bucket's start, the
+// keys (word << 32 | position in strip) are scattered by bucket, and an entry's
+// place is its bucket's start plus the number of keys of its bucket below its own.
+// Keys are unique and ordered as the reorder of Sec. 4 requires (column, then
+// RowInStrip, then CSR order), so duplicates need no special path.  A strip whose
+// largest bucket holds more than kBucketMax keys (columns bunched at a few values
+// far apart) is sorted by a bitonic network over the same keys instead.
+constexpr int kBucketMax = 64;
+constexpr int kTallSlots = 8;
+// From this height (next power of two) on, strips whose columns range over at
+// least kSpread times their entries take the bucketing pass too: five levels of
+// merging cost more than it does where buckets stay small.
+constexpr int kSpreadHeight = 32;
+constexpr int kSpread = 256;
+
+template <int HB, int NT, typename ET>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void from_csr_tall_kernel(
     int rows, int strips, int height, int bits, int nnz, const int* __restrict__ row_ptr,
     const int* __restrict__ col_ind, const ET* __restrict__ val_in, int* __restrict__ strip_ptr,
     uint32_t* __restrict__ col_word, ET* __restrict__ val_out, int* __restrict__ ws_count,
     int* __restrict__ ws_small, int* __restrict__ ws_big) {
-    constexpr int CAP = kWave * E;
-    constexpr int NBMAX = CAP / 4;
+    constexpr int E = kTallSlots, CAP = E * NT, NBMAX = CAP / 4;
     // The bucket count doubles up to NBMAX, so NBMAX must be a power of two
-    // (otherwise it would pass NBMAX and overrun bcnt/bstart).
-    static_assert((NBMAX & (NBMAX - 1)) == 0, "bucket capacity must be a power of two");
-    __shared__ uint64_t keys[kConvWaves][CAP];
-    __shared__ int bcnt[kConvWaves][NBMAX];
-    __shared__ int bstart[kConvWaves][NBMAX];
+    // (otherwise it would pass NBMAX and overrun start).
+    static_assert((NBMAX & (NBMAX - 1)) == 0 && NBMAX % NT == 0, "bucket capacity");
+    static_assert(HB + 1 <= kWave && NT >= 2 * kWave, "row table in one wave");
+    // Words in the first half (a search reads at most CAP past them), then values
+    // or keys in all of it.
+    __shared__ __align__(16) uint64_t keys[CAP];
+    __shared__ int start[NBMAX + 1];  // also the row table
+    __shared__ int red[3][NT / kWave];
+    const int tid = static_cast<int>(threadIdx.x);
     const int lane = lane_id();
-    const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
-    const int strip = xcd_logical_block(blockIdx.x, gridDim.x) * kConvWaves + wave;
-    if (strip >= strips) return;
+    const int wave = uniform(tid / kWave);
+    const int strip = xcd_logical_block(blockIdx.x, gridDim.x);
     const StripRows sr = load_strip_rows(strip, rows, height, row_ptr, lane);
-    const int n = sr.s1 - sr.s0;
-    if (lane == 0) {
-        strip_ptr[strip] = sr.s0;
+    const int s0 = uniform(sr.s0);
+    const int n = uniform(sr.s1) - s0;
+    if (tid == 0) {
+        strip_ptr[strip] = s0;
         if (strip == strips - 1) strip_ptr[strips] = nnz;
-    }
-    if (n > CAP) {
-        if (lane == 0) {
+        if (n > CAP) {
             if (n <= kWaveSortCap)
                 ws_small[atomicAdd(&ws_count[0], 1)] = strip;
             else
                 ws_big[atomicAdd(&ws_count[1], 1)] = strip;
         }
-        return;
     }
-    if (n == 0) return;
-    const int umax = uniform((n + kWave - 1) / kWave);
+    if (n > CAP || n == 0) return;
+    const int umax = (n + NT - 1) / NT;
+    LdsWord* const A = (LdsWord*)reinterpret_cast<uint32_t*>(keys);
+    const uint32_t rmask = (1u << bits) - 1u;
     uint32_t wd[E];
     ET v[E];
-    int cmin = INT_MAX, cmax = -1;
 #pragma unroll
     for (int u = 0; u < E; ++u) {
         wd[u] = 0u;
         v[u] = ET(0);
         if (u < umax) {
-            const int i = lane + kWave * u;
-            const int r = row_in_strip<HB>(sr.myrp, sr.s0 + i, 0);
-            if (i < n) {
-                const int c = col_ind[sr.s0 + i];
-                v[u] = val_in[sr.s0 + i];
-                wd[u] = (static_cast<uint32_t>(c) << bits) | static_cast<uint32_t>(r);
+            const int j = s0 + min(tid + NT * u, n - 1);
+            wd[u] = static_cast<uint32_t>(col_ind[j]) << bits;
+            v[u] = val_in[j];
+        }
+    }
+    if (tid <= HB) start[tid] = tid < sr.nr ? sr.myrp - s0 : n;  // wave 0: lane == tid
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (u >= umax) break;
+        const int i = tid + NT * u;
+        wd[u] |= static_cast<uint32_t>(row_in_strip<HB>(sr.myrp, s0 + min(i, n - 1), 0));
+        if (i < n) A[i] = wd[u];
+    }
+    __syncthreads();
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (u >= umax) break;
+        const int i = tid + NT * u;
+        if (i + 1 < n) {
+            const uint32_t nw = A[i + 1];
+            if ((nw & rmask) == (wd[u] & rmask) && nw < wd[u]) bad = true;
+        }
+    }
+    bad = __syncthreads_or(bad);
+    int cmin = INT_MAX, cmax = -1;
+    if (bad || HB >= kSpreadHeight) {  // uniform
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            if (tid + NT * u < n) {
+                const int c = static_cast<int>(wd[u] >> bits);
                 cmin = min(cmin, c);
                 cmax = max(cmax, c);
             }
         }
-    }
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) {
-        cmin = min(cmin, __shfl_xor(cmin, off));
-        cmax = max(cmax, __shfl_xor(cmax, off));
-    }
-    int nbk = 1;
-    while (nbk < NBMAX && nbk * 4 < n) nbk <<= 1;
-    // bucket(c) = ((c - cmin) * scale) >> 32 with scale = floor(2^32 nbk /
-    // range): non-decreasing in c and below nbk for c <= cmax.
-    const uint64_t range = static_cast<uint64_t>(cmax - cmin) + 1u;
-    const uint64_t scale = (static_cast<uint64_t>(nbk) << 32) / range;
-    int* cnt = bcnt[wave];
-    int* start = bstart[wave];
-    uint64_t* K = keys[wave];
-    for (int b = lane; b < nbk; b += kWave) cnt[b] = 0;
-    wave_lds_sync();
-    int bs[E];  // bucket << 16 | slot in bucket
-#pragma unroll
-    for (int u = 0; u < E; ++u) {
-        bs[u] = 0;
-        if (u < umax && lane + kWave * u < n) {
-            const uint32_t c = wd[u] >> bits;
-            const int bk = static_cast<int>((static_cast<uint64_t>(c - static_cast<uint32_t>(cmin)) * scale) >> 32);
-            bs[u] = (bk << 16) | atomicAdd(&cnt[bk], 1);
+        cmin = -wave_max(-cmin);
+        cmax = wave_max(cmax);
+        if (lane == 0) {
+            red[0][wave] = cmin;
+            red[1][wave] = cmax;
+        }
+        __syncthreads();
+        for (int w = 0; w < NT / kWave; ++w) {
+            cmin = min(cmin, red[0][w]);
+            cmax = max(cmax, red[1][w]);
         }
     }
-    wave_lds_sync();
-    // Exclusive scan of the counts: lane l sums buckets [l*per, (l+1)*per).
-    const int per = (nbk + kWave - 1) / kWave;
-    int mysum = 0, mymax = 0;
-    for (int k = 0; k < per; ++k) {
-        const int b = lane * per + k;
-        if (b < nbk) {
-            mysum += cnt[b];
-            mymax = max(mymax, cnt[b]);
-        }
-    }
-    int incl = mysum;
+    const bool spread = HB >= kSpreadHeight && cmax - cmin >= kSpread * n;
+    int pos[E];
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-    }
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) mymax = max(mymax, __shfl_xor(mymax, off));
-    int run = incl - mysum;
-    for (int k = 0; k < per; ++k) {
-        const int b = lane * per + k;
-        if (b < nbk) {
-            start[b] = run;
-            run += cnt[b];
-        }
-    }
-    wave_lds_sync();
-    if (mymax <= kBucketMax) {
+    for (int u = 0; u < E; ++u) pos[u] = tid + NT * u;
+    if (!bad && !spread) {
+        const int next_row = __shfl_down(sr.myrp, 1);
+        const int row_max = wave_max(lane < sr.nr ? next_row - sr.myrp : 0);
+        merge_runs_regs<HB, NT, E, true, true>(A, A, (LdsInt*)start, wd, pos, umax, true, n, tid, row_max, n,
+                                               [] { __syncthreads(); });
+        __syncthreads();
+    } else {
+        int nbk = 1;
+        while (nbk < NBMAX && nbk * 4 < n) nbk <<= 1;
+        for (int b = tid; b < NBMAX; b += NT) start[b] = 0;
+        __syncthreads();
+        // bucket(c) = ((c - cmin) * scale) >> 32 with scale = floor(2^32 nbk /
+        // range): non-decreasing in c and below nbk for c <= cmax.
+        const uint64_t range = static_cast<uint64_t>(cmax - cmin) + 1u;
+        const uint64_t scale = (static_cast<uint64_t>(nbk) << 32) / range;
+        int bs[E];  // bucket << 16 | slot in bucket
 #pragma unroll
         for (int u = 0; u < E; ++u) {
-            const int i = lane + kWave * u;
-            if (u < umax && i < n)
-                K[start[bs[u] >> 16] + (bs[u] & 0xffff)] = (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
-        }
-        wave_lds_sync();
-        int pos[E];
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            const int i = lane + kWave * u;
-            pos[u] = 0;
-            if (u < umax && i < n) {
-                const int bk = bs[u] >> 16;
-                const int b0 = start[bk], b1 = b0 + cnt[bk];
-                const uint64_t key = (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
-                int p = b0;
-                for (int k = b0; k < b1; ++k) p += K[k] < key ? 1 : 0;
-                pos[u] = p;
+            bs[u] = 0;
+            if (tid + NT * u < n) {
+                const uint32_t c = wd[u] >> bits;
+                const int bk = static_cast<int>((static_cast<uint64_t>(c - static_cast<uint32_t>(cmin)) * scale) >> 32);
+                bs[u] = (bk << 16) | atomicAdd(&start[bk], 1);
             }
         }
-        // The strip's sorted words, then its sorted values, go through the
-        // key buffer and out in order: a scatter into the strip's range would
-        // leave partly written lines (each reaching HBM more than once).
-        wave_lds_sync();
-        uint32_t* KW = reinterpret_cast<uint32_t*>(K);
+        __syncthreads();
+        // Counts to starts: thread t takes PER buckets from t * PER.
+        constexpr int PER = NBMAX / NT;
+        int cnt[PER], sum = 0, most = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            cnt[k] = start[tid * PER + k];
+            sum += cnt[k];
+            most = max(most, cnt[k]);
+        }
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int t = __shfl_up(incl, off);
+            if (lane >= off) incl += t;
+        }
+        most = wave_max(most);
+        if (lane == kWave - 1) red[0][wave] = incl;
+        if (lane == 0) red[2][wave] = most;
+        __syncthreads();
+        int run = incl - sum;
+        for (int w = 0; w < NT / kWave; ++w) {
+            if (w < wave) run += red[0][w];
+            most = max(most, red[2][w]);
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            start[tid * PER + k] = run;
+            run += cnt[k];
+        }
+        if (tid == NT - 1) start[NBMAX] = run;
+        __syncthreads();
+        if (most <= kBucketMax) {
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                const int i = tid + NT * u;
+                if (i < n)
+                    keys[start[bs[u] >> 16] + (bs[u] & 0xffff)] =
+                        (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                const int i = tid + NT * u;
+                if (i < n) {
+                    const int bk = bs[u] >> 16;
+                    const int b0 = start[bk], b1 = start[bk + 1];
+                    const uint64_t key = (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
+                    int p = b0;
+                    for (int k = b0; k < b1; ++k) p += keys[k] < key ? 1 : 0;
+                    pos[u] = p;
+                }
+            }
+        } else {
+            const int P = pow2_at_least(n);
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                const int i = tid + NT * u;
+                if (i < P) keys[i] = i < n ? (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i) : ~0ull;
+            }
+            __syncthreads();
+            bitonic_sort(keys, P, 0, tid, NT, [] { __syncthreads(); });
+            write_sorted_keys(keys, sr, n, val_in, col_word, val_out, tid, NT);
+            return;
+        }
+        __syncthreads();
 #pragma unroll
         for (int u = 0; u < E; ++u)
-            if (u < umax && lane + kWave * u < n) KW[pos[u]] = wd[u];
-        wave_lds_sync();
-        for (int i = lane; i < n; i += kWave) col_word[sr.s0 + i] = KW[i];
-        wave_lds_sync();
-        ET* KV = reinterpret_cast<ET*>(K);
-#pragma unroll
-        for (int u = 0; u < E; ++u)
-            if (u < umax && lane + kWave * u < n) KV[pos[u]] = v[u];
-        wave_lds_sync();
-        for (int i = lane; i < n; i += kWave) val_out[sr.s0 + i] = KV[i];
-    } else {
-        const int P = pow2_at_least(n);
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            const int i = lane + kWave * u;
-            if (i < n)
-                K[i] = (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
-            else if (i < P)
-                K[i] = ~0ull;
-        }
-        wave_lds_sync();
-        bitonic_sort(K, P, lane, kWave, [] { wave_lds_sync(); });
-        for (int i = lane; i < n; i += kWave) {
-            const uint64_t kk = K[i];
-            col_word[sr.s0 + i] = static_cast<uint32_t>(kk >> 32);
-            val_out[sr.s0 + i] = val_in[sr.s0 + static_cast<int>(static_cast<uint32_t>(kk))];
-        }
+            if (tid + NT * u < n) A[pos[u]] = wd[u];
+        __syncthreads();
     }
+    for (int i = tid; i < n; i += NT) col_word[s0 + i] = A[i];
+    __syncthreads();
+    ET* KV = reinterpret_cast<ET*>(keys);
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+        if (tid + NT * u < n) KV[pos[u]] = v[u];
+    __syncthreads();
+    for (int i = tid; i < n; i += NT) val_out[s0 + i] = KV[i];
 }
 
 // CMRS -> CSR at height 1: every strip is one row, so RowPtr is StripPtr and
@@ -1015,94 +1106,6 @@ __global__ __launch_bounds__(kConvThreads) void from_csr_rows_kernel(
     }
 }
 
-// ------------------------------------------------------------------ list kernels
-
-// One listed long strip of n entries by the whole 1024-thread workgroup, in K
-// (LDS, or the strip's workspace slice of 2n 64-bit words when keys_global;
-// passes over global memory then need an agent-scope fence before the
-// barrier).  Rows sorted by column: the words sit in K as 32-bit words in
-// strip order and each entry's place in the sorted strip is its index in its
-// own row plus, for every other row, the number of that row's words below
-// its own (binary search; the words of different rows never tie).  No second
-// buffer and no passes: one barrier after the words are in.  Otherwise a
-// bitonic network over (word, position) keys in K, which needs room for
-// pow2(n) <= 2n keys.  Forced inline, so that the LDS call site keeps the LDS
-// address space.
-template <int HB, typename ET>
-__device__ __forceinline__ void sort_strip_block(const StripRows& sr, int n, int bits,
-                                                 const int* __restrict__ col_ind, const ET* __restrict__ val_in,
-                                                 uint32_t* __restrict__ col_word, ET* __restrict__ val_out, uint64_t* K,
-                                                 bool keys_global, int* rt, int tid, int wave, int lane) {
-    uint32_t* W = reinterpret_cast<uint32_t*>(K);
-    const auto sync = [keys_global] {
-        if (keys_global) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
-        __syncthreads();
-    };
-    // Words in order, with the canonical-row check on the way: entry i and
-    // i + 1 of one row must not descend by column.
-    bool bad = false;
-    for (int base = wave * kWave; base < n; base += kBlockSortThreads) {
-        const int i = base + lane;
-        const int r = row_in_strip<HB>(sr.myrp, sr.s0 + i, 0);
-        const int rn = row_in_strip<HB>(sr.myrp, sr.s0 + i + 1, 0);
-        if (i < n) {
-            const int c = col_ind[sr.s0 + i];
-            W[i] = (static_cast<uint32_t>(c) << bits) | static_cast<uint32_t>(r);
-            if (i + 1 < n && rn == r && col_ind[sr.s0 + i + 1] < c) bad = true;
-        }
-    }
-    if (tid <= HB) rt[tid] = tid < sr.nr ? sr.myrp - sr.s0 : n;  // wave 0: lane == tid
-    if (keys_global) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
-    if (__syncthreads_or(bad) == 0) {
-        for (int i = tid; i < n; i += kBlockSortThreads) {
-            const uint32_t w = W[i];
-            const int r = static_cast<int>(w & static_cast<uint32_t>(HB - 1));
-            int pos = i - rt[r];
-            for (int x = 0; x < HB; ++x) {
-                if (x == r) continue;
-                const int lo = rt[x];
-                int a = lo, len = rt[x + 1] - lo;
-                while (len > 0) {
-                    const int half = len >> 1;
-                    if (W[a + half] < w) {
-                        a += half + 1;
-                        len -= half + 1;
-                    } else {
-                        len = half;
-                    }
-                }
-                pos += a - lo;
-            }
-            if (static_cast<unsigned>(pos) < static_cast<unsigned>(n)) {
-                col_word[sr.s0 + pos] = w;
-                val_out[sr.s0 + pos] = val_in[sr.s0 + i];
-            }
-        }
-    } else {
-        const int P = pow2_at_least(n);
-        sync();  // W is read above; the keys overwrite it
-        // P is a multiple of 64, so every lane of a wave takes each trip of
-        // this loop: the row lookup's cross-lane reads see all lanes.
-        for (int i = tid; i < P; i += kBlockSortThreads) {
-            const int r = row_in_strip<HB>(sr.myrp, sr.s0 + i, 0);
-            uint64_t key = ~0ull;
-            if (i < n)
-                key = (static_cast<uint64_t>((static_cast<uint32_t>(col_ind[sr.s0 + i]) << bits) |
-                                             static_cast<uint32_t>(r))
-                       << 32) |
-                      static_cast<uint32_t>(i);
-            K[i] = key;
-        }
-        sync();
-        bitonic_sort(K, P, tid, kBlockSortThreads, sync);
-        for (int i = tid; i < n; i += kBlockSortThreads) {
-            const uint64_t kk = K[i];
-            col_word[sr.s0 + i] = static_cast<uint32_t>(kk >> 32);
-            val_out[sr.s0 + i] = val_in[sr.s0 + static_cast<int>(static_cast<uint32_t>(kk))];
-        }
-    }
-}
-
 // Entries [lo, lo + len) of a sorted LDS array below w, for C entries at
 // once: the searches step together (binary lifting, as many steps as the
 // longest of the C ranges needs) so their LDS reads are in flight together.
@@ -1126,219 +1129,316 @@ __device__ inline void count_below(const uint32_t* S, const uint32_t (&w)[C], co
     }
 }
 
-// Rows of at most kLightRow entries are light; the light/heavy ranking below
-// is used while a strip's light rows hold at most kLightCap entries in all.
+// Rows of at most kLightRow entries are light, the others heavy.  A listed strip
+// of at most kHeavyMax heavy rows and kLightCap entries in light ones (one long
+// row among short ones, as skewed matrices have them) is streamed.
 constexpr int kLightRow = 64;
 constexpr int kLightCap = 512;
+constexpr int kHeavyMax = 2;
 
-// One listed strip of n <= 16*NT entries by a workgroup of NT threads;
-// thread t owns entries t + NT*u.  Rows sorted by column: the words go to
-// LDS (A) and each entry's place in the sorted strip is its rank among the
-// strip's words (the words of different rows never tie; equal words of one
-// row keep CSR order).  Long listed strips are mostly one or a few long rows
-// among short ones, and one binary search per (entry, other row) makes the
-// entries of a long row search every short row; instead:
-//  * the words of the light rows are gathered, in strip order, into LW (m of
-//    them); thread t takes light word t and counts the light words below it
-//    by reading all m (the same words for every lane: no bank conflicts, no
-//    dependent loads); that count is its rank among the light words, kept in
-//    LR, and its word goes to that rank in SL (the light words sorted);
-//  * an entry of a heavy row adds to its index in its row one binary search
-//    over SL, a light entry starts from its rank in LR, and every entry adds
-//    one binary search over each other heavy row.
-// With more than kLightCap light entries every row counts as heavy (one
-// search per other row).  Words and values then go to their places.  Global
-// loads (columns and values) are issued together, indices past the strip
-// clamped to its last entry, so a thread waits for memory once per strip;
-// prefetch() is called while they are in flight.  Rows not sorted: a bitonic
-// network over (word, position) keys in K, which holds pow2(n) keys.  K, A,
-// LW, LR and SL share the same LDS.
-template <int HB, int NT, typename ET, typename Prefetch>
-__device__ __forceinline__ void rank_strip_block(const StripRows& sr, int n, int bits,
-                                                 const int* __restrict__ col_ind, const ET* __restrict__ val_in,
-                                                 uint32_t* __restrict__ col_word, ET* __restrict__ val_out,
-                                                 uint64_t* K, int tid, Prefetch prefetch) {
-    constexpr int E = 16;
-    constexpr int CAP = E * NT;
-    constexpr int C = 4;  // slots searched together
-    static_assert(CAP + 3 * kLightCap <= 2 * CAP, "light lists must fit beside the words");
-    uint32_t* A = reinterpret_cast<uint32_t*>(K);
-    uint32_t* LW = A + CAP;
-    uint32_t* SL = LW + kLightCap;
-    int* LR = reinterpret_cast<int*>(SL + kLightCap);
-    const int lane = static_cast<int>(threadIdx.x) % kWave;
-    const int umax = (n + NT - 1) / NT;
-    int pos[E];
-    // Values: those of the first E/2 slots are loaded with the columns (one
-    // wait per strip for strips of up to 8*NT entries), the rest at the end.
-    ET vv[E / 2];
-    // Rows sorted by column: entry i and i + 1 of one row do not descend.
-    // Pairs inside a wave are checked before the first barrier, the pairs
-    // across waves (lane 63, next wave's lane 0) after it, from A.
+// The rows of a long strip, row x in lane x of every wave: its first entry in
+// the strip and its length (rows past the strip: n, 0).
+struct RunTable {
+    int lo, len;
+};
+template <int HB>
+__device__ inline RunTable run_table(const StripRows& sr, int n, int lane) {
+    RunTable t;
+    t.lo = lane < sr.nr ? sr.myrp - sr.s0 : n;
+    const int next = __shfl(t.lo, min(lane + 1, kWave - 1));
+    t.len = lane < HB ? next - t.lo : 0;
+    return t;
+}
+
+// A long strip that a workgroup streams: returns whether an entry descends (the
+// strip's output is then to be written again).  Thread t owns light entry t: its
+// rank among the light words comes from comparing it with all of them in LW (the
+// same words for every lane: no bank conflicts, no dependent loads), and SL takes
+// the light words in order.  A heavy entry's place is its index in its row plus
+// its count of light words below (a binary search over SL) plus one over each
+// other heavy row in global memory; a light entry's is its rank plus, for each
+// heavy row, the first entry that has counted it (H).  A heavy row's entries are read in order and
+// leave in nearly that order, so nothing of it is held: the strip costs two
+// barriers and a few KiB of LDS, and two workgroups share a CU.  (With the whole
+// strip's words in LDS, one workgroup of 1024 threads per CU, the listed strips of
+// the skewed 2*10^6-row workload, fp32, height 16, took 152 us at a quarter of the
+// VALU rate, 32 us a strip and workgroup, nearly all latency between barriers; now
+// 12 to 25 us a strip, 127 us for both lists.)
+template <int HB, int NT, typename ET>
+__device__ inline bool stream_strip(const StripRows& sr, const RunTable& rows_of, uint64_t heavy, int m, int rls,
+                                    int bits, const int* __restrict__ col_ind, const ET* __restrict__ val_in,
+                                    uint32_t* __restrict__ col_word, ET* __restrict__ val_out, uint32_t* LW,
+                                    uint32_t* SL, int* H, int tid, int lane) {
+    static_assert(NT >= kLightCap, "one light entry per thread");
+    constexpr int C = 4;  // entries of a heavy row searched together
+    const uint32_t rmask = (1u << bits) - 1u;
+    const int* __restrict__ col = col_ind + sr.s0;
+    const ET* __restrict__ vin = val_in + sr.s0;
     bool bad = false;
+    uint32_t w = 0;
+    ET v = ET(0);
+    int pos = 0;
+    const bool mine = tid < m;
     {
-        uint32_t c[E];
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            pos[u] = tid + NT * u;
-            if (u < umax) {
-                const int j = sr.s0 + min(pos[u], n - 1);
-                c[u] = static_cast<uint32_t>(col_ind[j]);
-                if (u < E / 2) vv[u % (E / 2)] = val_in[j];
-            }
-        }
-        prefetch();  // the caller's loads for its next strip, in flight with these
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            if (u < umax) {  // uniform: every lane runs the row lookup and the shuffles
-                const int i = pos[u];
-                const int r = row_in_strip<HB>(sr.myrp, sr.s0 + i, 0);
-                const int rend = __shfl(sr.myrp, r + 1) - sr.s0;  // end of the entry's row
-                const uint32_t cn = __shfl_down(c[u], 1);
-                if (lane < kWave - 1 && i + 1 < n && i + 1 < rend && cn < c[u]) bad = true;
-                if (i < n) A[i] = (c[u] << bits) | static_cast<uint32_t>(r);
-            }
+        const int r = row_in_strip<HB>(lane < HB ? rls : INT_MAX, tid, 0);
+        const int lo = __shfl(rows_of.lo, r), first = __shfl(rls, r);
+        if (mine) {
+            const int i = lo + tid - first;
+            w = (static_cast<uint32_t>(col[i]) << bits) | static_cast<uint32_t>(r);
+            v = vin[i];
+            LW[tid] = w;
         }
     }
-    bad = __syncthreads_or(bad) != 0;  // uniform from here on
-    bool bad_across = false;
-    if (!bad && lane == kWave - 1) {
-        const uint32_t rmask = (1u << bits) - 1u;
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            const int i = tid + NT * u;
-            if (u < umax && i + 1 < n) {
-                const uint32_t w = A[i], nw = A[i + 1];
-                if ((nw & rmask) == (w & rmask) && (nw >> bits) < (w >> bits)) bad_across = true;
-            }
+    __syncthreads();
+    if (mine) {
+        if (tid + 1 < m) {
+            const uint32_t nw = LW[tid + 1];
+            bad = (nw & rmask) == (w & rmask) && nw < w;
         }
-    }
-    // Row table in the lanes of every wave: lane x < HB holds row x's start
-    // and length in the strip (rows past the strip: start n, length 0).
-    const int rlo = lane < sr.nr ? sr.myrp - sr.s0 : n;
-    const int rnext = __shfl(rlo, min(lane + 1, kWave - 1));
-    const int rlen = lane < HB ? rnext - rlo : 0;
-    int m = 0;  // entries in light rows
-    {
-        int v = (lane < HB && rlen <= kLightRow) ? rlen : 0;
-#pragma unroll
-        for (int off = 1; off < HB; off <<= 1) v += __shfl_xor(v, off);
-        m = __shfl(v, 0);
-    }
-    const int lt = m <= kLightCap ? kLightRow : -1;  // rows of at most lt entries are light
-    if (lt < 0) m = 0;
-    const bool rlight = lane < HB && rlen <= lt;
-    int rls = rlight ? rlen : 0;  // row's first index in LW: exclusive prefix over the lanes
-#pragma unroll
-    for (int off = 1; off < HB; off <<= 1) {
-        const int t = __shfl_up(rls, off);
-        if (lane >= off) rls += t;
-    }
-    rls -= rlight ? rlen : 0;
-    const uint64_t heavy = ballot(lane < HB && rlen > lt && rlen > 0);
-    if (!bad && m > 0) {  // uniform
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            if (u < umax) {  // uniform: every lane runs the shuffles
-                const int i = tid + NT * u;
-                const uint32_t w = i < n ? A[i] : 0u;
-                const int r = static_cast<int>(w & static_cast<uint32_t>(HB - 1));
-                const int lo = __shfl(rlo, r), ls = __shfl(rls, r), lg = __shfl(rlight ? 1 : 0, r);
-                if (i < n && lg) LW[ls + i - lo] = w;
-            }
+        const uint4* LW4 = reinterpret_cast<const uint4*>(LW);
+        const auto add = [&](uint32_t a, int j) { pos += (a < w || (a == w && j < tid)) ? 1 : 0; };
+        int j = 0;
+#pragma unroll 1
+        for (; j + 8 <= m; j += 8) {
+            const uint4 p = LW4[j / 4], q = LW4[j / 4 + 1];
+            add(p.x, j); add(p.y, j + 1); add(p.z, j + 2); add(p.w, j + 3);
+            add(q.x, j + 4); add(q.y, j + 5); add(q.z, j + 6); add(q.w, j + 7);
         }
+        for (; j < m; ++j) add(LW[j], j);
+        SL[pos] = w;
     }
-    if (!bad) bad = __syncthreads_or(bad_across) != 0;
-    if (!bad) {
-        if (m > 0) {
-            // Rank of light word t among the light words; LW is 16-byte aligned
-            // and read four words at a time (the same words in every lane).
-            const uint4* LW4 = reinterpret_cast<const uint4*>(LW);
-            for (int t = tid; t < m; t += NT) {
-                const uint32_t w = LW[t];
-                int cnt = 0;
-                const auto add = [&](uint32_t a, int j) { cnt += (a < w || (a == w && j < t)) ? 1 : 0; };
-                int j = 0;
-                for (; j + 8 <= m; j += 8) {
-                    const uint4 p = LW4[j / 4], q = LW4[j / 4 + 1];
-                    add(p.x, j); add(p.y, j + 1); add(p.z, j + 2); add(p.w, j + 3);
-                    add(q.x, j + 4); add(q.y, j + 5); add(q.z, j + 6); add(q.w, j + 7);
+    const int rank = pos;
+    __syncthreads();
+    for (uint64_t hm = heavy; hm; hm &= hm - 1) {  // uniform
+        const int r = __ffsll(static_cast<unsigned long long>(hm)) - 1;
+        const int lo = __shfl(rows_of.lo, r), len = __shfl(rows_of.len, r);
+        if (mine) H[tid] = len;
+        __syncthreads();
+#pragma unroll 1
+        for (int i0 = 0; i0 < len; i0 += C * NT) {  // uniform
+            int c[C], nc[C], at[C], from[C], upto[C], cnt[C];
+            ET hv[C];
+            uint32_t hw[C];
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                at[k] = i0 + k * NT + tid;
+                const int i = lo + min(at[k], len - 1);
+                c[k] = col[i];
+                hv[k] = vin[i];
+                // The next entry's column: the next lane's, or loaded by the last lane.
+                nc[k] = lane == kWave - 1 ? col[lo + min(at[k] + 1, len - 1)] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const int shifted = __shfl_down(c[k], 1);
+                if (at[k] + 1 < len && (lane == kWave - 1 ? nc[k] : shifted) < c[k]) bad = true;
+                hw[k] = (static_cast<uint32_t>(c[k]) << bits) | static_cast<uint32_t>(r);
+                from[k] = 0;
+                upto[k] = m;
+            }
+            count_below<C>(SL, hw, from, upto, cnt);
+            // The light words below this entry and not below the one before it
+            // stand behind `at` entries of the row; noted at the last of them.
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const int before = __shfl_up(cnt[k], 1);
+                if (at[k] < len && cnt[k] > 0 && (lane == 0 || before != cnt[k])) atomicMin(&H[cnt[k] - 1], at[k]);
+            }
+#pragma unroll 1
+            for (uint64_t om = heavy & ~(1ull << r); om; om &= om - 1) {  // uniform
+                const int x = __ffsll(static_cast<unsigned long long>(om)) - 1;
+                const int xlo = __shfl(rows_of.lo, x), xlen = __shfl(rows_of.len, x);
+                // Entries of the other heavy row, in global memory, that sort
+                // before this one: columns below, or equal in an earlier row.
+                int below[C];
+#pragma unroll
+                for (int k = 0; k < C; ++k) below[k] = 0;
+#pragma unroll 1
+                for (int step = 1 << (31 - __clz(xlen)); step > 0; step >>= 1) {
+                    int y[C];
+#pragma unroll
+                    for (int k = 0; k < C; ++k) y[k] = col[xlo + min(below[k] + step, xlen) - 1];
+#pragma unroll
+                    for (int k = 0; k < C; ++k)
+                        if (below[k] + step <= xlen && (y[k] < c[k] || (x < r && y[k] == c[k]))) below[k] += step;
                 }
-                for (; j < m; ++j) add(LW[j], j);
-                LR[t] = cnt;
-                SL[cnt] = w;
+#pragma unroll
+                for (int k = 0; k < C; ++k) cnt[k] += below[k];
+            }
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                if (at[k] < len) {
+                    col_word[sr.s0 + at[k] + cnt[k]] = hw[k];
+                    val_out[sr.s0 + at[k] + cnt[k]] = hv[k];
+                }
+            }
+        }
+        __syncthreads();
+        // Entries of this row before the light word of rank t: the least note
+        // at t or behind it.
+        if (mine) {
+            int least = len;
+            for (int j = rank; j < m; ++j) least = min(least, H[j]);
+            pos += least;
+        }
+        __syncthreads();
+    }
+    if (mine && static_cast<unsigned>(pos) < static_cast<unsigned>(sr.s1 - sr.s0)) {
+        col_word[sr.s0 + pos] = w;
+        val_out[sr.s0 + pos] = v;
+    }
+    return bad;
+}
+
+// A long strip of at most NT*E entries by a merge of its row runs in LDS (A, B:
+// its words by place; rt: the rows' first places, HB + 1 of them): returns
+// whether an entry descends (nothing is written then).
+template <int HB, int NT, int E, typename ET>
+__device__ inline bool merge_strip_block(const StripRows& sr, int n, int row_max, int bits,
+                                         const int* __restrict__ col_ind, const ET* __restrict__ val_in,
+                                         uint32_t* __restrict__ col_word, ET* __restrict__ val_out, LdsWord* A,
+                                         LdsWord* B, const LdsInt* rt, int tid) {
+    const int umax = (n + NT - 1) / NT;
+    const uint32_t rmask = (1u << bits) - 1u;
+    uint32_t wd[E];
+    int pos[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        pos[u] = tid + NT * u;
+        wd[u] = static_cast<uint32_t>(col_ind[sr.s0 + min(pos[u], n - 1)]) << bits;
+    }
+#pragma unroll
+    for (int u = 0; u < E; ++u) {  // every lane runs the row lookup
+        wd[u] |= static_cast<uint32_t>(row_in_strip<HB>(sr.myrp, sr.s0 + min(pos[u], n - 1), 0));
+        if (pos[u] < n) A[pos[u]] = wd[u];
+    }
+    __syncthreads();
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (pos[u] + 1 < n) {
+            const uint32_t nw = A[pos[u] + 1];
+            if ((nw & rmask) == (wd[u] & rmask) && nw < wd[u]) bad = true;
+        }
+    }
+    if (__syncthreads_or(bad)) return true;
+    merge_runs_regs<HB, NT, E, false, false, true>(A, B, rt, wd, pos, umax, true, n, tid, row_max, n,
+                                            [] { __syncthreads(); });
+    ET v[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) v[u] = val_in[sr.s0 + min(tid + NT * u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (tid + NT * u < n && static_cast<unsigned>(pos[u]) < static_cast<unsigned>(n)) {
+            col_word[sr.s0 + pos[u]] = wd[u];
+            val_out[sr.s0 + pos[u]] = v[u];
+        }
+    }
+    return false;
+}
+
+// merge_strip_block for a strip of any length, keys in the strip's slice G
+// (2 n of them) of the workspace, C entries of a thread searched together.
+template <int HB, int NT, typename ET>
+__device__ inline bool merge_strip_global(const StripRows& sr, int n, int bits, const int* __restrict__ col_ind,
+                                          const ET* __restrict__ val_in, uint32_t* __restrict__ col_word,
+                                          ET* __restrict__ val_out, uint64_t* G, const int* rt, int tid) {
+    constexpr int C = 4;
+    const uint64_t rmask = (1ull << bits) - 1ull;
+    const int n64 = (n + kWave - 1) / kWave * kWave;  // whole waves: the row lookup's cross-lane reads see all lanes
+    for (int i = tid; i < n64; i += NT) {
+        const uint64_t k = strip_key<HB>(sr, n, i, bits, col_ind);
+        if (i < n) G[i] = k;
+    }
+    __syncthreads();
+    bool bad = false;
+    for (int i = tid; i + 1 < n; i += NT) {
+        const uint32_t w = static_cast<uint32_t>(G[i] >> 32), nw = static_cast<uint32_t>(G[i + 1] >> 32);
+        if ((nw & rmask) == (w & rmask) && nw < w) bad = true;
+    }
+    if (__syncthreads_or(bad)) return true;
+    uint64_t *src = G, *dst = G + n;
+    for (int k = 0; (1 << k) < HB; ++k) {
+        for (int i0 = tid; i0 < n; i0 += C * NT) {
+            uint64_t key[C];
+            int lo[C], len[C], cnt[C], own[C];
+            int top = 0;
+#pragma unroll
+            for (int v = 0; v < C; ++v) {
+                const int i = min(i0 + v * NT, n - 1);
+                key[v] = src[i];
+                const int run = static_cast<int>((key[v] >> 32) & (HB - 1)) >> k;
+                lo[v] = rt[(run ^ 1) << k];
+                len[v] = rt[((run ^ 1) + 1) << k] - lo[v];
+                own[v] = run & 1 ? i - len[v] : i;
+                cnt[v] = 0;
+                top |= len[v];
+            }
+            for (int step = top > 0 ? 1 << (31 - __clz(top)) : 0; step > 0; step >>= 1) {
+                uint64_t x[C];
+#pragma unroll
+                for (int v = 0; v < C; ++v) x[v] = src[max(lo[v] + min(cnt[v] + step, len[v]) - 1, 0)];
+#pragma unroll
+                for (int v = 0; v < C; ++v)
+                    if (cnt[v] + step <= len[v] && x[v] < key[v]) cnt[v] += step;
+            }
+#pragma unroll
+            for (int v = 0; v < C; ++v)
+                if (i0 + v * NT < n) dst[own[v] + cnt[v]] = key[v];
+        }
+        __syncthreads();
+        uint64_t* t = src;
+        src = dst;
+        dst = t;
+    }
+    write_sorted_keys(src, sr, n, val_in, col_word, val_out, tid, NT);
+    return false;
+}
+
+// A long strip with unsorted rows: a bitonic network over its keys, in the
+// workgroup's LDS K (TILE of them) or, for more, tile by tile, with the passes
+// between tiles in the strip's slice G of the workspace (its pow2(n) < 2 n keys).
+template <int HB, int NT, int TILE, typename ET>
+__device__ inline void bitonic_strip(const StripRows& sr, int n, int bits, const int* __restrict__ col_ind,
+                                     const ET* __restrict__ val_in, uint32_t* __restrict__ col_word,
+                                     ET* __restrict__ val_out, LdsKey* K, uint64_t* G, int tid) {
+    const int P = pow2_at_least(n);
+    const auto sync = [] { __syncthreads(); };
+    const int tile = min(P, TILE);  // a multiple of 64, so the row lookup sees whole waves
+    for (int t0 = 0; t0 < P; t0 += tile) {
+        for (int i = tid; i < tile; i += NT) K[i] = strip_key<HB>(sr, n, t0 + i, bits, col_ind);
+        __syncthreads();
+        bitonic_sort(K, tile, t0, tid, NT, sync);
+        if (P == tile) break;
+        for (int i = tid; i < tile; i += NT) G[t0 + i] = K[i];
+        __syncthreads();
+    }
+    if (P == tile) {
+        write_sorted_keys(K, sr, n, val_in, col_word, val_out, tid, NT);
+        return;
+    }
+    for (int size = 2 * tile; size <= P; size <<= 1) {
+        // Strides of whole tiles in the workspace, the rest of the size in LDS.
+        for (int stride = size >> 1; stride >= tile; stride >>= 1) {
+            for (int t = tid; t < P / 2; t += NT) {
+                const int i = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
+                const uint64_t a = G[i], b = G[i + stride];
+                if ((a > b) == ((i & size) == 0)) {
+                    G[i] = b;
+                    G[i + stride] = a;
+                }
             }
             __syncthreads();
         }
-        // Places.
-#pragma unroll
-        for (int u0 = 0; u0 < E; u0 += C) {
-            if (u0 >= umax) break;
-            uint32_t w[C];
-            int r[C], lo[C], len[C], cnt[C];
-            bool live[C];
-#pragma unroll
-            for (int v = 0; v < C; ++v) {
-                const int i = tid + NT * (u0 + v);
-                live[v] = i < n;
-                w[v] = live[v] ? A[i] : 0u;
-                r[v] = static_cast<int>(w[v] & static_cast<uint32_t>(HB - 1));
-                const int rl = __shfl(rlo, r[v]), ls = __shfl(rls, r[v]), lg = __shfl(rlight ? 1 : 0, r[v]);
-                const bool hv = live[v] && !lg;
-                if (live[v]) pos[u0 + v] = hv ? i - rl : LR[ls + i - rl];
-                lo[v] = 0;
-                len[v] = hv ? m : 0;
-            }
-            count_below<C>(SL, w, lo, len, cnt);
-#pragma unroll
-            for (int v = 0; v < C; ++v) pos[u0 + v] += cnt[v];
-            for (uint64_t hm = heavy; hm; hm &= hm - 1) {  // uniform
-                const int x = __ffsll(static_cast<unsigned long long>(hm)) - 1;
-                const int xlo = __shfl(rlo, x), xlen = __shfl(rlen, x);
-#pragma unroll
-                for (int v = 0; v < C; ++v) {
-                    lo[v] = xlo;
-                    len[v] = (live[v] && x != r[v]) ? xlen : 0;
-                }
-                count_below<C>(A, w, lo, len, cnt);
-#pragma unroll
-                for (int v = 0; v < C; ++v) pos[u0 + v] += cnt[v];
-            }
-        }
-        ET vl[E / 2];
-#pragma unroll
-        for (int u = E / 2; u < E; ++u)
-            if (u < umax) vl[u - E / 2] = val_in[sr.s0 + min(tid + NT * u, n - 1)];
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            const int i = tid + NT * u;
-            if (u < umax && i < n && static_cast<unsigned>(pos[u]) < static_cast<unsigned>(n)) {
-                col_word[sr.s0 + pos[u]] = A[i];
-                val_out[sr.s0 + pos[u]] = u < E / 2 ? vv[u % (E / 2)] : vl[u % (E / 2)];
-            }
-        }
-    } else {
-        const int P = pow2_at_least(n);
-        // P is a multiple of 64, so every lane of a wave takes each trip of
-        // this loop: the row lookup's cross-lane reads see all lanes.
-        for (int i = tid; i < P; i += NT) {
-            const int r = row_in_strip<HB>(sr.myrp, sr.s0 + i, 0);
-            uint64_t key = ~0ull;
-            if (i < n)
-                key = (static_cast<uint64_t>((static_cast<uint32_t>(col_ind[sr.s0 + i]) << bits) |
-                                             static_cast<uint32_t>(r))
-                       << 32) |
-                      static_cast<uint32_t>(i);
-            K[i] = key;
-        }
-        __syncthreads();
-        bitonic_sort(K, P, tid, NT, [] { __syncthreads(); });
-        for (int i = tid; i < n; i += NT) {
-            const uint64_t kk = K[i];
-            col_word[sr.s0 + i] = static_cast<uint32_t>(kk >> 32);
-            val_out[sr.s0 + i] = val_in[sr.s0 + static_cast<int>(static_cast<uint32_t>(kk))];
+        for (int t0 = 0; t0 < P; t0 += tile) {
+            for (int i = tid; i < tile; i += NT) K[i] = G[t0 + i];
+            __syncthreads();
+            bitonic_merge(K, tile, size, tile >> 1, t0, tid, NT, sync);
+            for (int i = tid; i < tile; i += NT) G[t0 + i] = K[i];
+            __syncthreads();
         }
     }
+    write_sorted_keys(G, sr, n, val_in, col_word, val_out, tid, NT);
 }
 
 // Row pointers of strip `strip` for lane <= rows of the strip (INT_MAX past
@@ -1348,38 +1448,45 @@ __device__ inline int strip_row_ptr(int strip, int rows, int height, const int* 
     return lane <= min(height, rows - r0) ? row_ptr[r0 + lane] : INT_MAX;
 }
 
-// Sorted conversion of the listed strips, both lists in one launch of one
-// 1024-thread workgroup per CU.  First the long strips (more than
-// kWaveSortCap entries): workgroup b takes list entry b first, then the next
-// untaken entry of a shared counter (ws_count[2], zero at launch), so strips
-// of very different lengths still spread evenly.  In LDS when the strip fits
-// (n <= kBlockSortCap, rank_strip_block), else in the strip's own slice of
-// the workspace [2*s0, 2*s1) (sort_strip_block).  A strip costs a chain of
-// dependent global loads (list entry, row pointers, then entries); the next
-// strip's list entry and row pointers are loaded while the current one is
-// sorted.  Then the short listed strips (at most kWaveSortCap entries): each
-// of the workgroup's 16 waves takes the next one from a second counter
-// (ws_count[3], zero at launch) and sorts it alone in its sixteenth of the
-// key buffer.  A workgroup whose long strips are done (or that drew none)
-// goes on to the short ones while others still sort long strips: run as two
-// launches, the CUs left idle by the last long strips waited for them.
+// Sorted conversion of the listed strips, both lists in one launch.  First the
+// short ones (at most kWaveSortCap entries), one wave each in its slice of the
+// key buffer, at a fixed stride.  Then the long ones: a workgroup takes the list
+// entry of its number, counted from the last workgroup (which has had the fewest
+// short strips), then the next untaken entry of a shared counter (ws_count[2],
+// zero at launch), so strips of very different lengths spread evenly.  (The other
+// way round, the workgroups that had sorted long strips until late started on
+// their short ones last: skewed 2*10^6 rows, fp32, height 16, 154 us against 127;
+// short ones by a counter too: 129 us, and slower at heights 2 to 8.)  One long
+// row among short ones is streamed, other strips are merged in LDS while they fit
+// (kBlockSortCap words twice), in the workspace beyond that, and strips with
+// unsorted rows go through a bitonic network afterwards.  A strip costs a chain
+// of dependent global loads (list entry, row pointers, then entries); the next
+// strip's list entry and row pointers are loaded while the current one is sorted.
 template <int HB, typename ET>
-__global__ __launch_bounds__(kBlockSortThreads) void sort_lists_kernel(
+__global__ __launch_bounds__(kBlockSortThreads) __attribute__((amdgpu_waves_per_eu(4))) void sort_lists_kernel(
     int rows, int height, int bits, const int* __restrict__ row_ptr, const int* __restrict__ col_ind,
     const ET* __restrict__ val_in, uint32_t* __restrict__ col_word, ET* __restrict__ val_out,
     int* __restrict__ ws_count, const int* __restrict__ ws_small, const int* __restrict__ ws_big,
     uint64_t* __restrict__ gkeys) {
-    constexpr int NW = kBlockSortThreads / kWave;
-    static_assert(kBlockSortCap >= NW * kWaveSortCap, "a short strip's keys per wave");
-    __shared__ uint64_t skeys[kBlockSortCap + merge_pad(kWaveSortCap / kWave)];
+    constexpr int NT = kBlockSortThreads, E = kBlockSortCap / NT;
+    constexpr int NWS = kBlockSortCap / kWaveSortCap;
+    static_assert(NWS == NT / kWave && 3 * kLightCap <= 2 * kBlockSortCap, "slices and light lists fit");
+    // Eight bytes in front: a clamped search reads one word before the first.
+    __shared__ __align__(16) uint64_t lds[2 + kBlockSortCap + merge_pad(kWaveSortCap / kWave)];
     __shared__ int rt[HB + 1];
     __shared__ int taken[2];
-    __shared__ int wrt[NW][HB + 1];
+    __shared__ int wrt[NWS][HB + 1];
+    uint64_t* const skeys = lds + 2;
     const int tid = static_cast<int>(threadIdx.x);
     const int lane = lane_id();
     const int wave = uniform(tid / kWave);
-    const int count = ws_count[1];
-    int item = static_cast<int>(blockIdx.x);
+    const int scount = ws_count[0], count = ws_count[1];
+    for (int it = static_cast<int>(blockIdx.x) * NWS + wave; it < scount; it += static_cast<int>(gridDim.x) * NWS)
+        sort_strip_mid<HB, kWaveSortCap / kWave, ET>(ws_small[it], rows, height, bits, row_ptr, col_ind, val_in,
+                                                     col_word, val_out, (LdsKey*)skeys + wave * kWaveSortCap,
+                                                     (LdsInt*)wrt[wave], lane);
+    __syncthreads();  // the long strips use the slices
+    int item = static_cast<int>(gridDim.x - 1 - blockIdx.x);
     if (item < count) {
         if (tid == 0) taken[0] = static_cast<int>(gridDim.x) + atomicAdd(&ws_count[2], 1);
         int strip = ws_big[item];
@@ -1398,17 +1505,40 @@ __global__ __launch_bounds__(kBlockSortThreads) void sort_lists_kernel(
             sr.s1 = __shfl(myrp, sr.nr);
             const int n = sr.s1 - sr.s0;
             const int nstrip = next < count ? ws_big[next] : 0;
-            int nmyrp = INT_MAX;
-            const auto prefetch = [&] {
-                if (next < count) nmyrp = strip_row_ptr(nstrip, rows, height, row_ptr, lane);
-            };
-            if (n <= kBlockSortCap) {
-                rank_strip_block<HB, kBlockSortThreads, ET>(sr, n, bits, col_ind, val_in, col_word, val_out, skeys,
-                                                            tid, prefetch);
+            const int nmyrp = next < count ? strip_row_ptr(nstrip, rows, height, row_ptr, lane) : INT_MAX;
+            const RunTable rows_of = run_table<HB>(sr, n, lane);
+            const bool light = lane < HB && rows_of.len <= kLightRow;
+            int incl = light ? rows_of.len : 0;  // light entries up to and with this row
+#pragma unroll
+            for (int off = 1; off < HB; off <<= 1) {
+                const int t = __shfl_up(incl, off);
+                if (lane >= off) incl += t;
+            }
+            const int m = __shfl(incl, HB - 1);
+            const int rls = incl - (light ? rows_of.len : 0);
+            const uint64_t heavy = ballot(lane < HB && !light);
+            uint64_t* const G = gkeys + 2 * static_cast<size_t>(sr.s0);
+            bool bad;
+            if (__popcll(heavy) <= kHeavyMax && m <= kLightCap) {
+                uint32_t* LW = reinterpret_cast<uint32_t*>(skeys);
+                bad = __syncthreads_or(stream_strip<HB, NT, ET>(sr, rows_of, heavy, m, rls, bits, col_ind, val_in,
+                                                                col_word, val_out, LW, LW + kLightCap,
+                                                                reinterpret_cast<int*>(LW + 2 * kLightCap), tid, lane));
             } else {
-                prefetch();
-                sort_strip_block<HB, ET>(sr, n, bits, col_ind, val_in, col_word, val_out,
-                                         gkeys + 2 * static_cast<size_t>(sr.s0), true, rt, tid, wave, lane);
+                if (wave == 0 && lane <= HB) rt[lane] = lane < HB ? rows_of.lo : n;
+                __syncthreads();
+                if (n <= kBlockSortCap) {
+                    LdsWord* A = (LdsWord*)reinterpret_cast<uint32_t*>(skeys);
+                    bad = merge_strip_block<HB, NT, E, ET>(sr, n, wave_max(rows_of.len), bits, col_ind, val_in,
+                                                           col_word, val_out, A, A + kBlockSortCap, (LdsInt*)rt, tid);
+                } else {
+                    bad = merge_strip_global<HB, NT, ET>(sr, n, bits, col_ind, val_in, col_word, val_out, G, rt, tid);
+                }
+            }
+            if (bad) {
+                __syncthreads();
+                bitonic_strip<HB, NT, kBlockSortCap, ET>(sr, n, bits, col_ind, val_in, col_word, val_out,
+                                                         (LdsKey*)skeys, G, tid);
             }
             __syncthreads();  // the next item reuses skeys and rt
             item = next;
@@ -1417,12 +1547,6 @@ __global__ __launch_bounds__(kBlockSortThreads) void sort_lists_kernel(
             myrp = nmyrp;
         }
     }
-    const int scount = ws_count[0];
-    LdsKey* slice = (LdsKey*)skeys + wave * kWaveSortCap;
-    const int nwaves = static_cast<int>(gridDim.x) * NW;
-    for (int it = static_cast<int>(blockIdx.x) * NW + wave; it < scount; it += nwaves)
-        sort_strip_mid<HB, kWaveSortCap / kWave, ET>(ws_small[it], rows, height, bits, row_ptr, col_ind, val_in,
-                                                     col_word, val_out, slice, (LdsInt*)wrt[wave], lane);
 }
 
 __global__ void validate_csr_kernel(int rows, int cols, int nnz, const int* __restrict__ row_ptr,
@@ -1449,12 +1573,12 @@ struct Conv {
 };
 
 // Both lists of strips the first kernel could not sort (sort_lists_kernel):
-// one workgroup per CU, or fewer when the lists cannot be that long.
+// two workgroups per CU, or fewer when the lists cannot be that long.
 template <int HB, typename ET>
 void launch_sort_lists(const Conv& cv, const FromCsrWorkspaceLayout& L, const int* row_ptr, const int* col_ind,
                        const ET* vin, uint32_t* col_word, ET* vout, int* ws_count, const int* ws_small,
                        const int* ws_big, uint64_t* gkeys, hipStream_t stream) {
-    constexpr size_t NW = kBlockSortThreads / kWave;
+    constexpr size_t NW = kBlockSortCap / kWaveSortCap;
     const size_t want = std::max<size_t>(L.big_cap, (L.small_cap + NW - 1) / NW);
     const int g = static_cast<int>(std::max<size_t>(1, std::min<size_t>(want, kBlockSortGrid)));
     hipLaunchKernelGGL((sort_lists_kernel<HB, ET>), dim3(g), dim3(kBlockSortThreads), 0, stream, cv.rows,
@@ -1484,13 +1608,11 @@ hipError_t from_csr_g(const Conv& cv, const int* row_ptr, const int* col_ind, co
     return hipGetLastError();
 }
 
-// Tall strips: the bucket kernel (one wave per strip of up to kWaveSortCap
-// entries), then the same list kernel for longer strips.
-template <int HB, typename ET>
-hipError_t from_csr_bucket(const Conv& cv, const int* row_ptr, const int* col_ind, const void* val_in,
-                           int* strip_ptr, uint32_t* col_word, void* val_out, void* workspace, hipStream_t stream) {
-    constexpr int E = kWaveSortCap / kWave;
-    const int blocks = (cv.strips + kConvWaves - 1) / kConvWaves;
+// Tall strips (from_csr_tall_kernel), then the same list kernel for longer
+// ones.
+template <int HB, int NT, typename ET>
+hipError_t from_csr_tall(const Conv& cv, const int* row_ptr, const int* col_ind, const void* val_in, int* strip_ptr,
+                         uint32_t* col_word, void* val_out, void* workspace, hipStream_t stream) {
     const auto* vin = static_cast<const ET*>(val_in);
     auto* vout = static_cast<ET*>(val_out);
     const FromCsrWorkspaceLayout L = from_csr_workspace_layout(cv.rows, cv.nnz, cv.height);
@@ -1500,21 +1622,35 @@ hipError_t from_csr_bucket(const Conv& cv, const int* row_ptr, const int* col_in
     int* ws_big = reinterpret_cast<int*>(ws + L.big_off);
     auto* gkeys = reinterpret_cast<uint64_t*>(ws + L.global_off);
     hipLaunchKernelGGL(set_ints_kernel, dim3(1), dim3(64), 0, stream, ws_count, 4, 0);
-    hipLaunchKernelGGL((from_csr_bucket_kernel<HB, E, ET>), dim3(blocks), dim3(kConvThreads), 0, stream, cv.rows,
-                       cv.strips, cv.height, cv.bits, cv.nnz, row_ptr, col_ind, vin, strip_ptr, col_word, vout,
-                       ws_count, ws_small, ws_big);
+    hipLaunchKernelGGL((from_csr_tall_kernel<HB, NT, ET>), dim3(cv.strips), dim3(NT), 0, stream, cv.rows, cv.strips,
+                       cv.height, cv.bits, cv.nnz, row_ptr, col_ind, vin, strip_ptr, col_word, vout, ws_count,
+                       ws_small, ws_big);
     launch_sort_lists<HB, ET>(cv, L, row_ptr, col_ind, vin, col_word, vout, ws_count, ws_small, ws_big, gkeys,
                               stream);
     return hipGetLastError();
 }
 
+// The mean strips that a workgroup of 128, 256 or 512 threads takes one at a time
+// (from_csr_tall_kernel): nearly up to its 1024, 2048 or 4096 entries, since a
+// longer strip goes to the lists.  Below, a wave of the group kernel holds a strip
+// (512 entries) and is faster: means of 384 to 432 entries 149/74/200 us against
+// 185/112/248 (band of 81, fp32, height 8; band of 21, fp64, height 32; 27-point
+// stencil, fp64, height 16).
+constexpr double kTall128Mean = 450.0, kTall256Mean = 900.0, kTall512Mean = 1850.0, kTallEnd = 3800.0;
+
 template <int HB, typename ET>
 hipError_t from_csr_hb(const Conv& cv, const int* row_ptr, const int* col_ind, const void* val_in,
                        int* strip_ptr, uint32_t* col_word, void* val_out, void* workspace, hipStream_t stream) {
-    if constexpr (HB >= kBucketMinHeight) {
-        if (static_cast<double>(cv.nnz) >= kBucketMinMean * static_cast<double>(cv.strips))
-            return from_csr_bucket<HB, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
-                                           stream);
+    const double mean = static_cast<double>(cv.nnz) / cv.strips;
+    if (mean >= kTall128Mean && mean < kTallEnd) {
+        if (mean < kTall256Mean)
+            return from_csr_tall<HB, 128, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
+                                              stream);
+        if (mean < kTall512Mean)
+            return from_csr_tall<HB, 256, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
+                                              stream);
+        return from_csr_tall<HB, 512, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
+                                          stream);
     }
     const ConvShape sh = conv_shape(cv.nnz, cv.strips, HB);
 #define CMRS_FROM_G(GG, EE)                                                                                      \

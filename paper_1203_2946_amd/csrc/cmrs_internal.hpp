@@ -67,6 +67,22 @@ hipError_t launch_from_csr(int32_t rows, int32_t cols, int32_t nnz, const int32_
 hipError_t launch_to_csr(const cmrs_mat_t* A, int32_t* row_ptr, int32_t* col_ind, void* val_out,
                          hipStream_t stream);
 
+// Whether a strip-group or column-block walk with g lanes per strip reads its
+// streams with non-temporal loads.  They keep x in L2, but a line that a load
+// uses in part is gone when the next load of the same strip wants the rest, so
+// they pay only where the g lanes' words or values fill more than a line of 128
+// bytes.  Non-temporal against cached, us, listed by g: 5-point stencil fp64 8-16
+// 58/36, 100 000 Poisson(16) rows fp64 16 16.7/12.4, 27-point stencil fp64 16
+// 198/158, fp32 32 62/54, skewed rows fp32 4-16 105/88; but 2^20 Poisson(16) rows
+// fp64 32 186/189, fp32 64 110/114, 27-point stencil fp64 64 149/152, band fp32
+// 64 47/48.  Column blocks: fp32 height 32 (32 lanes) 105/90, fp64 height 8 (8)
+// 185/150, height 32 (32) 122/124.  Split schedule: fp64 height 16 100/93, bf16
+// height 32 67/62.
+constexpr bool stream_past_cache(int g, size_t value_bytes) { return g * (value_bytes > 4 ? value_bytes : 4) > 128; }
+template <typename VT>
+constexpr bool stream_past_cache(int g) {
+    return stream_past_cache(g, sizeof(VT));
+}
 hipError_t launch_spmv(const cmrs_mat_t* A, const void* x, void* y, cmrs_dtype_t xy_dtype, int variant,
                        hipStream_t stream);
 // Lanes per strip of the strip-group SpMV: about 8 entries per lane for the

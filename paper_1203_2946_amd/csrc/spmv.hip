@@ -213,17 +213,9 @@ hipError_t launch_one(const Launch& L) {
     return hipGetLastError();
 }
 
-template <typename VT, typename XT, typename AT, int HB, int G, bool NT>
-hipError_t launch_group_g(const Launch& L) {
+template <typename VT, typename XT, typename AT, int HB, int G, int U, bool NT>
+hipError_t launch_group_u(const Launch& L) {
     constexpr int NG = kWave / G;
-    // Loads per lane in one step: about 1.5 times the entries a lane gets
-    // from spmv_group_width (4 up to height 8, 8 above), so that most strips
-    // take one step while few loads go to the clamped slots past their end:
-    // 6 up to height 8, 12 at height 32; 8 at height 16, where 12 was mixed.
-    // Cold, against 8 everywhere: 2^20 Poisson(16) rows, fp32, height
-    // 2/4/32 179/155/125 -> 164/146/112 us; the skewed rows, fp64, height 32
-    // 162 -> 154 us (6 there: 173 us).
-    constexpr int U = HB <= 8 ? 6 : (HB <= 16 ? 8 : 12);
     const int waves = (L.strips + NG - 1) / NG;
     const int blocks = (waves + kSpmvWaves - 1) / kSpmvWaves;
     hipLaunchKernelGGL((spmv_group_kernel<HB, G, U, NT, VT, XT, AT>), dim3(blocks), dim3(kSpmvThreads), 0, L.stream,
@@ -233,6 +225,26 @@ hipError_t launch_group_g(const Launch& L) {
     return hipGetLastError();
 }
 
+template <typename VT, typename XT, typename AT, int HB, int G, bool NT>
+hipError_t launch_group_g(const Launch& L) {
+    // Loads per lane in one step: about 1.5 times the entries a lane gets
+    // from spmv_group_width (4 up to height 8, 8 above), so that most strips
+    // take one step while few loads go to the clamped slots past their end:
+    // 6 up to height 8, 12 at height 32; 8 at height 16, where 12 was mixed.
+    // Cold, against 8 everywhere: 2^20 Poisson(16) rows, fp32, height
+    // 2/4/32 179/155/125 -> 164/146/112 us; the skewed rows, fp64, height 32
+    // 162 -> 154 us (6 there: 173 us).
+    constexpr int U = HB <= 8 ? 6 : (HB <= 16 ? 8 : 12);
+    // fp64 up to height 8 with a mean strip of at most 3.6 entries per lane:
+    // 4 hold it too, and the address units, busy most of the time, see a third
+    // fewer 8-byte loads (27-point stencil of 2*10^6 rows: height 2 158 -> 145
+    // us, height 8 149 -> 136; fp32 and bf16 were mixed, 55 -> 49 to 47 -> 49).
+    if constexpr (HB <= 8 && sizeof(VT) == 8) {
+        if (static_cast<double>(L.A->nnz) <= 3.6 * G * static_cast<double>(L.strips))
+            return launch_group_u<VT, XT, AT, HB, G, 4, NT>(L);
+    }
+    return launch_group_u<VT, XT, AT, HB, G, U, NT>(L);
+}
 
 template <typename VT, typename XT, typename AT, int HB, bool NT>
 hipError_t launch_group(const Launch& L) {
@@ -265,7 +277,7 @@ hipError_t launch_concurrent_g(const Launch& L) {
     const int waves = (L.strips + NG - 1) / NG;
     const int blocks_per_cb = (waves + kSpmvWaves - 1) / kSpmvWaves;
     auto* part = static_cast<AT*>(L.partial);
-    hipLaunchKernelGGL((spmv_colblock_concurrent_kernel<HB, G, U, true, VT, XT, AT>), dim3(blocks_per_cb * L.nb),
+    hipLaunchKernelGGL((spmv_colblock_concurrent_kernel<HB, G, U, stream_past_cache<VT>(G), VT, XT, AT>), dim3(blocks_per_cb * L.nb),
                        dim3(kSpmvThreads), 0, L.stream, L.A->rows, L.strips, L.A->height, L.A->bits, L.A->strip_ptr,
                        L.A->col_word, static_cast<const VT*>(L.A->val), static_cast<const XT*>(L.x), part, L.split,
                        L.nb, 4 * U * G);
@@ -346,9 +358,10 @@ int spmv_group_width(int nnz, int strips, int hb) {
 }
 
 int resolve_spmv_variant(const cmrs_mat_t* A, int variant) {
-    (void)A;
     if (variant != CMRS_SPMV_AUTO) return variant;
-    return CMRS_SPMV_GROUP_NT;
+    const int strips = (A->rows + A->height - 1) / A->height;
+    const int g = strips > 0 ? spmv_group_width(A->nnz, strips, next_pow2(A->height)) : 64;
+    return stream_past_cache(g, dtype_bytes(A->val_dtype)) ? CMRS_SPMV_GROUP_NT : CMRS_SPMV_GROUP;
 }
 
 hipError_t launch_spmv(const cmrs_mat_t* A, const void* x, void* y, cmrs_dtype_t xy_dtype, int variant,
@@ -403,8 +416,8 @@ hipError_t launch_spmv_colblock(const cmrs_mat_t* A, const void* x, void* y, int
                                 const int* split, int schedule, void* workspace, hipStream_t stream) {
     const int strips = (A->rows + A->height - 1) / A->height;
     if (strips == 0) return hipSuccess;
-    variant = resolve_spmv_variant(A, variant);
-    if (nb <= 1) return dispatch(variant, Launch{A, strips, x, y, nullptr, 1, stream});
+    if (nb <= 1) return dispatch(resolve_spmv_variant(A, variant), Launch{A, strips, x, y, nullptr, 1, stream});
+    if (variant == CMRS_SPMV_AUTO) variant = CMRS_SPMV_GROUP_NT;
     if (schedule == CMRS_COLBLOCK_PHASED) return launch_spmv_phased(A, x, y, nb, split, stream);
     Launch L{A, strips, x, y, split, nb, stream};
     if (schedule == CMRS_COLBLOCK_CONCURRENT) L.partial = workspace;

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kSpmvThreads) void spmv_split_kernel(
             const SplitHeavy hv = heavy[ck.heavy];
             LdsAcc<HB, AT> acc{buf[wave]};
             acc.init(lane);
-            accumulate_run<U, NT, VT, XT, AT>(acc, ck.lo, ck.hi, bits, word, val, x, lane);
+            accumulate_run<U, true, VT, XT, AT>(acc, ck.lo, ck.hi, bits, word, val, x, lane);
             const AT s = acc.finish(lane);
             const int r = lane / GW;
             if (hv.nchunks == 1) {
@@ -275,7 +275,7 @@ hipError_t launch_split_g(const cmrs_mat_t* A, const SplitShape& s, const void* 
     // lane gets there; skewed rows, cold, h = 8: fp64 139 -> 134 us, fp32
     // 103 -> 98 us), kSplitU above (12 was slower at h = 16: 124 -> 131 us).
     constexpr int SU = HB <= 8 ? 6 : kSplitU;
-    hipLaunchKernelGGL((spmv_split_kernel<HB, G, SU, true, VT, XT, AT>), dim3(chunk_blocks + group_blocks),
+    hipLaunchKernelGGL((spmv_split_kernel<HB, G, SU, stream_past_cache<VT>(G), VT, XT, AT>), dim3(chunk_blocks + group_blocks),
                        dim3(kSpmvThreads), 0, stream, A->rows, strips, A->height, A->bits, A->strip_ptr, A->col_word,
                        static_cast<const VT*>(A->val), static_cast<const XT*>(x), static_cast<XT*>(y), s.long_len,
                        chunk_blocks, s.max_chunks, reinterpret_cast<const int*>(base),

@@ -20,7 +20,7 @@
 //
 // The batched path runs that body from one persistent kernel: waves take
 // work tiles (a matrix and a range of its strips) from per-XCD queue counters
-// in the plan until every queue is empty; the last wave out resets the
+// in the plan until every queue is empty; the last workgroup out resets the
 // counters, so the same plan can be launched again and replayed from a HIP
 // graph.  A grid stride over strip passes (the listing's loop over strips in
 // the paper's appendix) is the special case of one tile per wave.
@@ -880,58 +880,104 @@ __device__ inline void spmm_tile_rb(const SpmmMat& m, int s0, int s1, AT* buf, i
     }
 }
 
-// Work queues, one per XCD: queue x hands out the tiles [x*n/8, (x+1)*n/8)
-// through the counter queue[x * 16] (one 64-byte line each).  Workgroup b
-// runs on XCD b mod 8 and drains that XCD's queue first, so neighbouring
-// tiles (and the parts of X they gather) stay in one L2; then it takes tiles
-// left in the other queues.  queue[kQueueDone] counts finished waves.  All
-// counters are zero at launch and again when the last wave leaves.
+// Work queues, one per XCD: queue x holds the tiles [x*n/8, (x+1)*n/8).
+// Workgroup b runs on XCD b mod 8.  Its waves start on the tiles of their own
+// numbers in that XCD's queue; what is left of the queue comes through the
+// counter queue[x * 16] (one 64-byte line each), so neighbouring tiles (and the
+// parts of X they gather) stay in one L2; then a wave takes tiles left in the
+// other queues.  queue[kQueueDone + x * 8] counts the finished workgroups of XCD
+// x, and queue[kQueueAllDone] the XCDs whose workgroups all have.  All counters are zero at
+// launch and again when the last workgroup leaves.
+//
+// An atomic on one address takes about 5 ns of all its askers' time and 2 us of
+// its own wave's, so few are asked: none for the first tile, none of a queue that
+// a wave of the workgroup has found empty, and one count per workgroup at the end,
+// on eight addresses.  That count is relaxed: a release or acquire at agent scope
+// writes back or invalidates the whole L2, and it orders nothing here that the
+// tickets' own return does not (a workgroup counts itself out after its waves'
+// last tickets have come back, and the next launch sees the reset as any write of
+// this one).  128.9 M entries, 32 matrices, tiles of 4096, fp64 height 8 / fp32
+// height 4: 736/556 us with tickets for every tile, eight failing ones and an
+// ordered count per wave; 595/441 with the empty queues noted and a count per
+// workgroup; 562/414 with the count relaxed; 555/405 now.  (Reading the counters
+// before asking was slower: 690/488.)
 constexpr int kQueueStride = 16;
-constexpr int kQueueDone = kNumXcd * kQueueStride;
+constexpr int kQueueDone = kNumXcd * kQueueStride, kDoneStride = 8;
+constexpr int kQueueAllDone = kQueueDone + kNumXcd * kDoneStride;
+static_assert((kQueueAllDone + 1) * sizeof(unsigned) <= kSpmmHeaderBytes, "counters fit the header");
 
 template <typename VT, typename XT, typename AT>
 __global__ __launch_bounds__(kSpmmMaxWaves * kWave) __attribute__((amdgpu_waves_per_eu(sizeof(AT) == 8 ? 4 : 1))) void spmm_persistent_kernel(
     const SpmmMat* __restrict__ mats, const SpmmTile* __restrict__ tiles, int ntiles, unsigned* __restrict__ queue,
-    int waves_total, int wave_slots) {
+    int wave_slots) {
     extern __shared__ __align__(16) unsigned char spmm_lds[];
+    __shared__ unsigned drained;  // bit x: a wave of the workgroup has found queue x empty
+    if (threadIdx.x == 0) drained = 0;
+    __syncthreads();
     const int lane = lane_id();
+    const int wpb = static_cast<int>(blockDim.x) / kWave;
+    const int grid = static_cast<int>(gridDim.x);
     const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
     AT* buf = reinterpret_cast<AT*>(spmm_lds) + static_cast<size_t>(wave) * wave_slots;
     const int home = static_cast<int>(blockIdx.x) % kNumXcd;
-    for (int a = 0; a < kNumXcd; ++a) {
-        const int qx = (home + a) % kNumXcd;
-        const long long lo = static_cast<long long>(qx) * ntiles / kNumXcd;
-        const long long hi = static_cast<long long>(qx + 1) * ntiles / kNumXcd;
-        for (;;) {
-            unsigned c = 0;
-            if (lane == 0)
-                c = __hip_atomic_fetch_add(&queue[qx * kQueueStride], 1u, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-            c = static_cast<unsigned>(uniform(static_cast<int>(__shfl(c, 0))));
-            const long long t = lo + c;
-            if (t >= hi) break;
-            const SpmmTile tile = tiles[t];
-            const SpmmMat m = mats[tile.mat];
-            switch (m.hb) {
-                case 1: spmm_tile_rb<1, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
-                case 2: spmm_tile_rb<2, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
-                case 4: spmm_tile_rb<4, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
-                case 8: spmm_tile_rb<8, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
-                case 16: spmm_tile_rb<16, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
-                default: spmm_tile_rb<32, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+    const auto first_tile = [&](int x) { return static_cast<int>(static_cast<long long>(x) * ntiles / kNumXcd); };
+    // Workgroups of XCD x; the first tile of queue x that its counter hands out.
+    const auto groups_of = [&](int x) { return (grid - x + kNumXcd - 1) / kNumXcd; };
+    const auto counted_from = [&](int x) { return first_tile(x) + groups_of(x) * wpb; };
+    int t = first_tile(home) + static_cast<int>(blockIdx.x) / kNumXcd * wpb + wave;
+    if (t >= first_tile(home + 1)) t = -1;
+    int tried = 0;  // queues this wave has left behind, home first
+    for (;;) {
+        while (t < 0 && tried < kNumXcd) {
+            const int qx = (home + tried) % kNumXcd;
+            const int handed = first_tile(qx + 1) - counted_from(qx);
+            if (handed > 0 &&
+                !((__hip_atomic_load(&drained, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> qx) & 1u)) {
+                unsigned c = 0;
+                if (lane == 0)
+                    c = __hip_atomic_fetch_add(&queue[qx * kQueueStride], 1u, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                c = static_cast<unsigned>(uniform(static_cast<int>(c)));
+                if (c < static_cast<unsigned>(handed)) {
+                    t = counted_from(qx) + static_cast<int>(c);
+                    break;
+                }
+                if (lane == 0)
+                    __hip_atomic_fetch_or(&drained, 1u << qx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
+            ++tried;
         }
+        if (t < 0) break;
+        const SpmmTile tile = tiles[t];
+        const SpmmMat m = mats[tile.mat];
+        switch (m.hb) {
+            case 1: spmm_tile_rb<1, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+            case 2: spmm_tile_rb<2, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+            case 4: spmm_tile_rb<4, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+            case 8: spmm_tile_rb<8, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+            case 16: spmm_tile_rb<16, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+            default: spmm_tile_rb<32, VT, XT, AT>(m, tile.s0, tile.s1, buf, lane); break;
+        }
+        t = -1;
     }
-    // Every wave has taken its last ticket from every queue before it counts
-    // itself out, so the wave that counts last may reset them for the next
-    // launch.
-    if (lane == 0) {
-        const unsigned d =
-            __hip_atomic_fetch_add(&queue[kQueueDone], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (d == static_cast<unsigned>(waves_total - 1)) {
-            for (int x = 0; x < kNumXcd; ++x)
-                __hip_atomic_store(&queue[x * kQueueStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&queue[kQueueDone], 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    // Every wave of the workgroup has taken its last ticket from every queue
+    // before the workgroup counts itself out, so the one that counts last may
+    // reset the counters for the next launch.
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned d = __hip_atomic_fetch_add(&queue[kQueueDone + home * kDoneStride], 1u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+        if (d == static_cast<unsigned>(groups_of(home)) - 1u) {
+            const unsigned x = __hip_atomic_fetch_add(&queue[kQueueAllDone], 1u, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+            if (x == static_cast<unsigned>(min(grid, kNumXcd)) - 1u) {
+                for (int k = 0; k < kNumXcd; ++k) {
+                    __hip_atomic_store(&queue[k * kQueueStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&queue[kQueueDone + k * kDoneStride], 0u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                }
+                __hip_atomic_store(&queue[kQueueAllDone], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
 }
@@ -1055,7 +1101,24 @@ hipError_t launch_spmm(const cmrs_mat_t* A, int nrhs, const void* X, int ldx, vo
 SpmmPlanShape spmm_plan_shape(int count, const cmrs_mat_t* mats, const int* nrhs, int tile_nnz, int group,
                               std::vector<SpmmTile>* tiles_out) {
     SpmmPlanShape sh{};
-    const int target = tile_nnz > 0 ? tile_nnz : 32768;
+    // Entries per tile.  A batch of at least kRounds tiles of kTileMost entries for
+    // each of the chip's waves takes those (larger ones end unevenly, smaller ones
+    // start over too often); below that every wave gets one tile, of a size that
+    // leaves some waves over and no second round for a few tiles.  Below kTileSmall
+    // entries 32768.  (us at 32768 / 6144 / 4096 / 2048 / 1024 entries: 32
+    // matrices of 129 M, fp64 722/558/540/567/685, fp32 487/402/401/429/525; 8 of
+    // 17.8 M, fp64 363/113/125/138/142; 4 of 7.2 M, fp32 274/67/48/37/93; 3 of
+    // 1.1 M, fp64 338/66/47/27/17.)
+    constexpr double kTileMost = 4096.0, kTileLeast = 1024.0, kTileSmall = 262144.0;
+    constexpr double kWaves = 256.0 * 4.0 * kSpmmMaxWaves, kRounds = 3.0;
+    double target = tile_nnz;
+    if (tile_nnz <= 0) {
+        double entries = 0.0;
+        for (int i = 0; i < count; ++i) entries += mats[i].nnz;
+        target = entries < kTileSmall                      ? 32768.0
+                 : entries < kRounds * kWaves * kTileMost ? std::max(kTileLeast, entries / (0.85 * kWaves))
+                                                           : kTileMost;
+    }
     // Tiles grouped by (height bucket, right-hand-side bucket), so that waves
     // running at the same time mostly execute the same code.
     std::vector<std::pair<int, int>> order;
@@ -1106,7 +1169,10 @@ hipError_t build_spmm_plan(int count, const cmrs_mat_t* mats, const int* nrhs, c
     const size_t wave_bytes = spmm_wave_lds_bytes(std::max(1, sh.max_slots), at);
     const int wpb = spmm_waves_per_block(wave_bytes);
     const int bpc = blocks_per_cu > 0 ? blocks_per_cu : 4;
-    const long long want_blocks = (static_cast<long long>(sh.tiles) + wpb - 1) / wpb;
+    // Enough workgroups for a wave per tile in every XCD's queue, if they fit.
+    const long long per_queue = (static_cast<long long>(sh.tiles) + kNumXcd - 1) / kNumXcd;
+    const long long want_blocks = std::min<long long>((sh.tiles + wpb - 1) / wpb + kNumXcd,
+                                                      (per_queue + wpb - 1) / wpb * kNumXcd);
     const int grid = static_cast<int>(std::max(1LL, std::min(static_cast<long long>(cus) * bpc, want_blocks)));
     cmrs_spmm_plan_t P{};
     P.count = count;
@@ -1139,15 +1205,15 @@ hipError_t launch_spmm_batched(const cmrs_spmm_plan_t* plan, hipStream_t stream)
     switch (plan->val_dtype) {
         case CMRS_R64F:
             hipLaunchKernelGGL((spmm_persistent_kernel<double, double, double>), grid, block, lds, stream, mats,
-                               tiles, plan->tiles, queue, plan->waves, wave_slots);
+                               tiles, plan->tiles, queue, wave_slots);
             break;
         case CMRS_R32F:
             hipLaunchKernelGGL((spmm_persistent_kernel<float, float, float>), grid, block, lds, stream, mats, tiles,
-                               plan->tiles, queue, plan->waves, wave_slots);
+                               plan->tiles, queue, wave_slots);
             break;
         default:
             hipLaunchKernelGGL((spmm_persistent_kernel<bf16_t, float, float>), grid, block, lds, stream, mats, tiles,
-                               plan->tiles, queue, plan->waves, wave_slots);
+                               plan->tiles, queue, wave_slots);
             break;
     }
     return hipGetLastError();

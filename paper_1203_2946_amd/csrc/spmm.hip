@@ -39,15 +39,32 @@ constexpr int kSpmmMaxWaves = 4;
 constexpr size_t kSpmmWaveLdsMax = 65536;
 constexpr int kSpmmMaxPassesPerWave = 8;
 
-template <typename T>
-__device__ inline T nt_load(const T* p) {
-    return __builtin_nontemporal_load(p);
+template <bool NT, typename T>
+__device__ inline T stream_load(const T* p) {
+    if constexpr (!NT) {
+        return *p;
+    } else if constexpr (std::is_same<T, bf16_t>::value) {
+        bf16_t v;
+        v.bits = __builtin_nontemporal_load(&p->bits);
+        return v;
+    } else {
+        return __builtin_nontemporal_load(p);
+    }
 }
-__device__ inline bf16_t nt_load(const bf16_t* p) {
-    bf16_t v;
-    v.bits = __builtin_nontemporal_load(&p->bits);
-    return v;
-}
+
+// Stream loads go through the cache: a strip's lanes use its lines in part, and
+// a line read past the cache is fetched again for the rest.  (Non-temporal against
+// cached, us, matrices in turn: 131 071 Poisson(16) rows, 5 columns, fp64 33.9/30.5;
+// 300 000-row Laplacian, 8 columns, fp64 30.7/26.3; fp32 band of 40, 5 columns,
+// 90.3/82.9; the batch of 32 matrices, fp64 563/543, fp32 422/414.  The one loss,
+// gathers over 10^6 random rows of 30 entries, fp64, 5 columns: 660/666.)  Only a
+// single launch for one or two right-hand sides with more than 16 lanes per strip,
+// whose entries fill whole lines, keeps x in L2 by reading
+// past it: 10^6 random rows of 30 entries, fp64, 32 and 64 lanes, 314/330 and
+// 309/326, fp32 194/203 and 188/199, bf16, 2 columns, 287/293 and 278/288;
+// but 8 and 16 lanes, 400 000 rows of 8, fp64 34/27 and 33/26, fp32 29/22 and
+// 28/22, bf16 34/21 and 30/21.
+constexpr int kNtLanesLog = 4;
 
 template <int RB>
 struct SpmmUnroll {
@@ -87,8 +104,8 @@ __device__ inline void spmm_load_step(const SpmmMat& m, int base, int G, int hi,
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int j = max(min(base + u * G, hi - 1), 0);
-        w[u] = nt_load(m.word + j);
-        v[u] = nt_load(val + j);
+        w[u] = m.word[j];
+        v[u] = val[j];
     }
 }
 
@@ -287,8 +304,8 @@ __device__ inline void spmm_load_chunk(const SpmmMat& m, int g, int G, int hi, i
         const int j = g + (k * CS::C + c) * G;
         const int jv = max(min(min(j, hi - 1), m.nnz - CS::C), 0);
         t.d[k] = j - jv;
-        t.w[k] = __builtin_nontemporal_load(reinterpret_cast<const WV*>(m.word + jv));
-        t.v[k] = __builtin_nontemporal_load(reinterpret_cast<const VV*>(val + jv));
+        t.w[k] = *reinterpret_cast<const WV*>(m.word + jv);
+        t.v[k] = *reinterpret_cast<const VV*>(val + jv);
     }
 }
 
@@ -334,7 +351,7 @@ __device__ inline int blk_entry(int base, int G, int u) {
     return base + (u / kBlk) * kBlk * G + u % kBlk;
 }
 
-template <int U, typename VT>
+template <bool NT, int U, typename VT>
 __device__ inline void spmm_load_blk(const SpmmMat& m, int base, int G, int hi, BlkStream<U, VT>& t) {
     typedef typename SVec<uint32_t, kBlk>::type WV;
     typedef typename SVec<VT, kBlk>::type VV;
@@ -344,8 +361,8 @@ __device__ inline void spmm_load_blk(const SpmmMat& m, int base, int G, int hi, 
         const int j = base + k * kBlk * G;
         const int jv = max(min(min(j, hi - 1), m.nnz - kBlk), 0);
         t.d[k] = j - jv;
-        t.w[k] = __builtin_nontemporal_load(reinterpret_cast<const WV*>(m.word + jv));
-        t.v[k] = __builtin_nontemporal_load(reinterpret_cast<const VV*>(val + jv));
+        t.w[k] = stream_load<NT>(reinterpret_cast<const WV*>(m.word + jv));
+        t.v[k] = stream_load<NT>(reinterpret_cast<const VV*>(val + jv));
     }
 }
 
@@ -654,7 +671,7 @@ __device__ inline void spmm_tile_blk(const SpmmMat& m, int s0, int s1, AT* __res
     int lo_n = sp[min(s + S, s1)], hi_n = sp[min(s + S + 1, s1)];
     int base = lo + kBlk * e;
     BlkStream<U, VT> t;
-    spmm_load_blk<U, VT>(m, base, G, hi, t);
+    spmm_load_blk<false, U, VT>(m, base, G, hi, t);
     for (int sb = s0;;) {
         XT xv[U][RB];
 #pragma unroll
@@ -666,7 +683,7 @@ __device__ inline void spmm_tile_blk(const SpmmMat& m, int s0, int s1, AT* __res
         const int nb = base + U * G;
         const bool more = ballot(nb < hi) != 0ull;
         BlkStream<U, VT> t2;
-        spmm_load_blk<U, VT>(m, more ? nb : lo_n + kBlk * e, G, more ? hi : hi_n, t2);
+        spmm_load_blk<false, U, VT>(m, more ? nb : lo_n + kBlk * e, G, more ? hi : hi_n, t2);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool ok = blk_entry(base, G, u) < hi;
@@ -703,7 +720,7 @@ __device__ inline void spmm_tile_blk(const SpmmMat& m, int s0, int s1, AT* __res
 // one pass per wave this is faster than the branch-free pipelined step, which
 // adds +0.0 for every clamped entry (measured 11-16 % on 2*10^6-row band and
 // stencil matrices).  It sums the same products in the same order.
-template <int HB, int RB, typename VT, typename XT, typename AT>
+template <bool NT, int HB, int RB, typename VT, typename XT, typename AT>
 __device__ inline void spmm_pass_small(const SpmmMat& m, int sb, int s_end, AT* __restrict__ buf, int lane) {
     static_assert(RB <= 2, "one or two right-hand-side slots");
     constexpr int U = SpmmUnroll<RB>::U;
@@ -723,8 +740,8 @@ __device__ inline void spmm_pass_small(const SpmmMat& m, int sb, int s_end, AT* 
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int j = min(base + u * G, hi - 1);
-                w[u] = nt_load(m.word + j);
-                v[u] = nt_load(val + j);
+                w[u] = stream_load<NT>(m.word + j);
+                v[u] = stream_load<NT>(val + j);
             }
             XT xv[U][RB];
 #pragma unroll
@@ -751,7 +768,7 @@ __device__ inline void spmm_pass_small(const SpmmMat& m, int sb, int s_end, AT* 
 
 // spmm_pass_small with blocked stream data (BlkStream): the products of the
 // same entries, added in the same order as spmm_tile_blk.
-template <int HB, int RB, typename VT, typename XT, typename AT>
+template <bool NT, int HB, int RB, typename VT, typename XT, typename AT>
 __device__ inline void spmm_pass_small_blk(const SpmmMat& m, int sb, int s_end, AT* __restrict__ buf, int lane) {
     static_assert(RB <= 2, "one or two right-hand-side slots");
     constexpr int U = SpmmUnroll<RB>::U;
@@ -766,7 +783,7 @@ __device__ inline void spmm_pass_small_blk(const SpmmMat& m, int sb, int s_end, 
         const size_t ldx = static_cast<size_t>(m.ldx);
         for (int base = lo + kBlk * e; base < hi; base += U * G) {
             BlkStream<U, VT> t;
-            spmm_load_blk<U, VT>(m, base, G, hi, t);
+            spmm_load_blk<NT, U, VT>(m, base, G, hi, t);
             XT xv[U][RB];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -860,11 +877,17 @@ __global__ __launch_bounds__(kSpmmMaxWaves * kWave) void spmm_kernel(SpmmMat m, 
         for (int i = 0; i < HB * RB; ++i) buf[i * kWave + lane] = AT(0);
         if constexpr (spmm_blk_type<VT>()) {
             if (m.nnz >= kBlk) {
-                spmm_pass_small_blk<HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
+                if (m.g_log > kNtLanesLog)
+                    spmm_pass_small_blk<true, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
+                else
+                    spmm_pass_small_blk<false, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
                 return;
             }
         }
-        spmm_pass_small<HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
+        if (m.g_log > kNtLanesLog)
+            spmm_pass_small<true, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
+        else
+            spmm_pass_small<false, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
     } else {
         spmm_tile_nv<HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
     }
@@ -899,7 +922,8 @@ __device__ inline void spmm_tile_rb(const SpmmMat& m, int s0, int s1, AT* buf, i
 // this one).  128.9 M entries, 32 matrices, tiles of 4096, fp64 height 8 / fp32
 // height 4: 736/556 us with tickets for every tile, eight failing ones and an
 // ordered count per wave; 595/441 with the empty queues noted and a count per
-// workgroup; 562/414 with the count relaxed; 555/405 now.  (Reading the counters
+// workgroup; 562/414 with the count relaxed; 555/405 with
+// the first tile free of a ticket; 533/394 with cached stream loads.  (Reading the counters
 // before asking was slower: 690/488.)
 constexpr int kQueueStride = 16;
 constexpr int kQueueDone = kNumXcd * kQueueStride, kDoneStride = 8;
@@ -1105,10 +1129,10 @@ SpmmPlanShape spmm_plan_shape(int count, const cmrs_mat_t* mats, const int* nrhs
     // each of the chip's waves takes those (larger ones end unevenly, smaller ones
     // start over too often); below that every wave gets one tile, of a size that
     // leaves some waves over and no second round for a few tiles.  Below kTileSmall
-    // entries 32768.  (us at 32768 / 6144 / 4096 / 2048 / 1024 entries: 32
-    // matrices of 129 M, fp64 722/558/540/567/685, fp32 487/402/401/429/525; 8 of
-    // 17.8 M, fp64 363/113/125/138/142; 4 of 7.2 M, fp32 274/67/48/37/93; 3 of
-    // 1.1 M, fp64 338/66/47/27/17.)
+    // entries 32768.  (us at 6144 / 4096 / 2048 entries: 32 matrices of 129 M,
+    // fp64 545/533/553, fp32 393/394/421; 8 of 17.8 M, fp64 99/112/120; 4 of 7.2 M,
+    // fp32 60/44/34; 3 of 1.1 M, fp64 60/42/24 and 16 at 1024.  At 32768, with
+    // non-temporal stream loads: 722, 487, 363, 274 and 338.)
     constexpr double kTileMost = 4096.0, kTileLeast = 1024.0, kTileSmall = 262144.0;
     constexpr double kWaves = 256.0 * 4.0 * kSpmmMaxWaves, kRounds = 3.0;
     double target = tile_nnz;

@@ -163,8 +163,13 @@ def _check(status: int, where: str):
 
 
 def _stream(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # The raw handle: torch.cuda.current_stream() builds a Stream object for it, 2.8 us of
+    # the 8.3 us of a small product (5.9 without).
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t: torch.Tensor | None) -> int | None:

@@ -41,8 +41,7 @@ DATA_PATH = os.path.join(_HERE, "data", "selector_timings.npz")
 _L = cmrs.lib
 
 
-def _s():
-    return torch.cuda.current_stream().cuda_stream
+_s = cmrs._stream
 
 
 def _p(t):

@@ -509,7 +509,7 @@ __device__ inline void write_sorted_keys(const Key* K, const StripRows& sr, int 
 // entries per lane had four: 249 us).  Strips like these went to the lists or,
 // bunched columns at height 16 and up, through the bitonic network: band of 129,
 // fp32, height 8/16/32 1068/3252/3313 -> 212/282/456 us; 27-point stencil, fp64,
-// height 32 640 -> 284 us; Poisson(48) rows, fp64, height 32 3840 -> 231 us.
+// height 32 640 -> 270 us; Poisson(48) rows, fp64, height 32 3840 -> 231 us.
 //
 // Rows not sorted: one bucketing pass, whatever the height: entries fall into NB
 // buckets of about equal width over the strip's column range [cmin, cmax] (NB
@@ -524,10 +524,14 @@ __device__ inline void write_sorted_keys(const Key* K, const StripRows& sr, int 
 constexpr int kBucketMax = 64;
 constexpr int kTallSlots = 8;
 // From this height (next power of two) on, strips whose columns range over at
-// least kSpread times their entries take the bucketing pass too: five levels of
-// merging cost more than it does where buckets stay small.
+// least kSpread times their entries take the bucketing pass too, as long as no
+// bucket then holds more than kSpreadBucketMax: five levels of merging cost more
+// than it does (60 000 Poisson(15) rows, fp64, height 32: 23.9 us merged, 18.6
+// bucketed).  Clustered columns, counted in vain, pay about 10 % (27-point stencil
+// of 10^6 rows 270 -> 300 us with the line at 16), so the line lies above those.
 constexpr int kSpreadHeight = 32;
-constexpr int kSpread = 256;
+constexpr int kSpread = 32;
+constexpr int kSpreadBucketMax = 16;
 
 template <int HB, int NT, typename ET>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void from_csr_tall_kernel(
@@ -624,13 +628,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
     int pos[E];
 #pragma unroll
     for (int u = 0; u < E; ++u) pos[u] = tid + NT * u;
-    if (!bad && !spread) {
-        const int next_row = __shfl_down(sr.myrp, 1);
-        const int row_max = wave_max(lane < sr.nr ? next_row - sr.myrp : 0);
-        merge_runs_regs<HB, NT, E, true, true>(A, A, (LdsInt*)start, wd, pos, umax, true, n, tid, row_max, n,
-                                               [] { __syncthreads(); });
-        __syncthreads();
-    } else {
+    bool merge = !bad && !spread;
+    if (!merge) {
         int nbk = 1;
         while (nbk < NBMAX && nbk * 4 < n) nbk <<= 1;
         for (int b = tid; b < NBMAX; b += NT) start[b] = 0;
@@ -681,7 +680,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
         }
         if (tid == NT - 1) start[NBMAX] = run;
         __syncthreads();
-        if (most <= kBucketMax) {
+        if (most <= (bad ? kBucketMax : kSpreadBucketMax)) {
 #pragma unroll
             for (int u = 0; u < E; ++u) {
                 const int i = tid + NT * u;
@@ -702,6 +701,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
                     pos[u] = p;
                 }
             }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < E; ++u)
+                if (tid + NT * u < n) A[pos[u]] = wd[u];
+        } else if (!bad) {
+            merge = true;  // A still holds the words
+            if (tid <= HB) start[tid] = tid < sr.nr ? sr.myrp - s0 : n;
         } else {
             const int P = pow2_at_least(n);
 #pragma unroll
@@ -715,9 +721,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
             return;
         }
         __syncthreads();
-#pragma unroll
-        for (int u = 0; u < E; ++u)
-            if (tid + NT * u < n) A[pos[u]] = wd[u];
+    }
+    if (merge) {
+        const int next_row = __shfl_down(sr.myrp, 1);
+        const int row_max = wave_max(lane < sr.nr ? next_row - sr.myrp : 0);
+        merge_runs_regs<HB, NT, E, true, true>(A, A, (LdsInt*)start, wd, pos, umax, true, n, tid, row_max, n,
+                                               [] { __syncthreads(); });
         __syncthreads();
     }
     for (int i = tid; i < n; i += NT) col_word[s0 + i] = A[i];
@@ -1637,16 +1646,22 @@ hipError_t from_csr_tall(const Conv& cv, const int* row_ptr, const int* col_ind,
 // 185/112/248 (band of 81, fp32, height 8; band of 21, fp64, height 32; 27-point
 // stencil, fp64, height 16).
 constexpr double kTall128Mean = 450.0, kTall256Mean = 900.0, kTall512Mean = 1850.0, kTallEnd = 3800.0;
+// Up to four strips per CU, where a strip's latency is the kernel's time, take twice
+// the threads (128 / 256 threads, height 32: 98 Poisson(15) strips, fp64, 18.7/13.9 us,
+// 625 strips 19.1/14.8, 625 27-point stencil strips, fp32, 22.5/17.0; 1875 strips
+// 23.9/25.1; 256 / 512 threads, 98 Poisson(40) strips 20.4/15.1).
+constexpr int kTallFew = 1024;
 
 template <int HB, typename ET>
 hipError_t from_csr_hb(const Conv& cv, const int* row_ptr, const int* col_ind, const void* val_in,
                        int* strip_ptr, uint32_t* col_word, void* val_out, void* workspace, hipStream_t stream) {
     const double mean = static_cast<double>(cv.nnz) / cv.strips;
     if (mean >= kTall128Mean && mean < kTallEnd) {
-        if (mean < kTall256Mean)
+        const bool few = cv.strips <= kTallFew;
+        if (mean < kTall256Mean && !few)
             return from_csr_tall<HB, 128, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
                                               stream);
-        if (mean < kTall512Mean)
+        if (mean < (few ? kTall256Mean : kTall512Mean))
             return from_csr_tall<HB, 256, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
                                               stream);
         return from_csr_tall<HB, 512, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,

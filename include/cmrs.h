@@ -214,7 +214,7 @@ cmrs_status_t cmrs_spmv(const cmrs_mat_t *A, const void *x, void *y, cmrs_dtype_
  * summed in a different order) and are deterministic.
  *   col_blocks   1 .. 64; 1 means no blocking (plan of zero bytes).
  *   variant      accumulation variant as for cmrs_spmv (the concurrent
- *                schedule always uses strip groups with non-temporal loads).
+ *                schedule always uses strip groups).
  * The plan depends only on A's strip_ptr and col_word; rebuild it when they
  * change.  CMRS_ERR_INVALID_VALUE if A is not sorted.
  */
@@ -339,7 +339,7 @@ cmrs_status_t cmrs_spmm(const cmrs_mat_t *A, int32_t nrhs, const void *X, int32_
  * ldx_i, ldy_i) and the tile list.  cmrs_spmm_batched() then launches
  * plan->grid workgroups that take tiles from the queues until they are
  * empty: one queue per XCD over a contiguous eighth of the tile list, drained
- * first by that XCD's workgroups; the last wave to finish resets the queues,
+ * first by that XCD's workgroups; the last workgroup to finish resets the queues,
  * so the same plan can be launched again, one launch at a time per plan, and
  * captured into a HIP graph.  Tile t of matrix i is computed exactly as
  * cmrs_spmm computes those strips with the plan's group width (clamped to
@@ -366,7 +366,10 @@ cmrs_status_t cmrs_spmm(const cmrs_mat_t *A, int32_t nrhs, const void *X, int32_
  */
 typedef struct {
     int32_t tile_nnz;       /* stored entries per work tile (rounded to whole
-                               strip passes); 0 = 32768                        */
+                               strip passes); 0 = by the batch's entries: 32768
+                               below 2^18, then about 3500 tiles of at least
+                               1024, from 5*10^7 on 4096 (and 32768 if `desc`
+                               holds only that many tiles)                     */
     int32_t group;          /* entry slots per strip, a power of two; 0 = from
                                each matrix's mean strip length                 */
     int32_t blocks_per_cu;  /* resident 256-thread workgroups per compute unit;

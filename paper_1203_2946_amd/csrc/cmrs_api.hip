@@ -442,11 +442,23 @@ cmrs_status_t cmrs_spmm_plan(int32_t count, const cmrs_mat_t* mats, const int32_
         if (it != ys.end() && it->lo < hi)
             return fail(CMRS_ERR_INVALID_VALUE, "X of matrix %d overlaps Y of matrix %d", j, it->idx);
     }
-    const size_t need = cmrs_spmm_plan_bytes(count, mats, nrhs, tuning);
+    size_t need = cmrs_spmm_plan_bytes(count, mats, nrhs, tuning);
+    int tile_nnz = tuning ? tuning->tile_nnz : 0;
+    if (tile_nnz == 0 && desc && desc_bytes < need) {
+        // A buffer sized for tiles of 32768 entries, the default of small batches.
+        cmrs_spmm_tuning_t coarse{};
+        if (tuning) coarse = *tuning;
+        coarse.tile_nnz = 32768;
+        const size_t least = cmrs_spmm_plan_bytes(count, mats, nrhs, &coarse);
+        if (desc_bytes >= least) {
+            tile_nnz = coarse.tile_nnz;
+            need = least;
+        }
+    }
     if (!desc || desc_bytes < need)
         return fail(CMRS_ERR_WORKSPACE, "plan buffer of %zu bytes needed, %zu given", need, desc_bytes);
     if (reinterpret_cast<uintptr_t>(desc) & 15u) return fail(CMRS_ERR_INVALID_VALUE, "plan buffer not 16-byte aligned");
-    return from_hip(cmrs::build_spmm_plan(count, mats, nrhs, X, ldx, Y, ldy, xy_dtype, tuning ? tuning->tile_nnz : 0,
+    return from_hip(cmrs::build_spmm_plan(count, mats, nrhs, X, ldx, Y, ldy, xy_dtype, tile_nnz,
                                           tuning ? tuning->group : 0, tuning ? tuning->blocks_per_cu : 0, desc, plan,
                                           stream),
                     "cmrs_spmm_plan");

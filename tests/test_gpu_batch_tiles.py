@@ -53,3 +53,29 @@ def _absolute(M):
     from paper_1203_2946_amd import cmrs
     rp, ci, v = cmrs.to_csr(M)
     return rp, ci, v.abs(), M.cols, M.height
+
+
+def test_default_plan_in_a_buffer_of_coarse_tiles():
+    """A buffer sized for tiles of 32768 entries takes the default tuning too;
+    one byte less is refused with either."""
+    import ctypes
+    from paper_1203_2946_amd import cmrs
+    A = synth.random_csr(60_000, 60_000, max_row=12, seed=3, canonical=True)
+    rp, ci, v, _ = G.upload(A, "f64")
+    M = cmrs.from_csr(rp, ci, v, A.cols, 4, sort=True)
+    X = torch.as_tensor(synth.uniform_vector(A.cols, seed=1).reshape(A.cols, 1), device="cuda")
+    assert int(M.nnz) >= 262144
+    descs, one = (cmrs.CmrsMatDesc * 1)(M.desc()), (ctypes.c_int32 * 1)(1)
+    least = int(cmrs.lib.cmrs_spmm_plan_bytes(1, descs, one, ctypes.byref(cmrs.SpmmTuning(32768, 0, 0, 0))))
+    assert least < int(cmrs.lib.cmrs_spmm_plan_bytes(1, descs, one, None))
+    Y = torch.full_like(X, float("nan"))
+    xp, yp = (ctypes.c_void_p * 1)(X.data_ptr()), (ctypes.c_void_p * 1)(Y.data_ptr())
+    buf = torch.empty(least, dtype=torch.uint8, device="cuda")
+    for tuning in (None, ctypes.byref(cmrs.SpmmTuning(32768, 0, 0, 0))):
+        plan = cmrs.SpmmPlanStruct()
+        args = (1, descs, one, xp, one, yp, one, 0, tuning, buf.data_ptr())
+        assert cmrs.lib.cmrs_spmm_plan(*args, least - 1, ctypes.byref(plan), cmrs._stream()) == cmrs.CMRS_ERR_WORKSPACE
+        assert cmrs.lib.cmrs_spmm_plan(*args, least, ctypes.byref(plan), cmrs._stream()) == cmrs.CMRS_OK
+        Y.fill_(float("nan"))
+        assert cmrs.lib.cmrs_spmm_batched(ctypes.byref(plan), cmrs._stream()) == cmrs.CMRS_OK
+        assert torch.equal(Y, cmrs.spmm(M, X))

@@ -41,6 +41,7 @@
 
 #include "cmrs_device.hpp"
 #include "cmrs_internal.hpp"
+#include "merge_search.hpp"
 
 namespace cmrs {
 
@@ -170,7 +171,7 @@ __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt,
     const auto merge_level = [&](int k) {
         if (k > 0) sync();
         const int longest = min(row_max << k, n_max);
-        const int top = longest > 0 ? 4 << (31 - __clz(longest)) : 0;
+        const int top = merge_first_step(longest);
         const int first = lds_address(A) - 4;
         // Level k of the slots u0 .. u0 + C - 1, their searches in step.
         const auto level = [&](auto count, int u0) {
@@ -187,10 +188,7 @@ __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt,
 #pragma unroll
                 for (int v = 0; v < C; ++v) x[v] = lds_word(CLAMP ? min(cur[v] + step, last[v]) : cur[v] + step);
 #pragma unroll
-                for (int v = 0; v < C; ++v) {
-                    const int t = cur[v] + step;
-                    cur[v] = static_cast<int>(t <= last[v]) & static_cast<int>(x[v] < wd[u0 + v]) ? t : cur[v];
-                }
+                for (int v = 0; v < C; ++v) cur[v] = merge_step(cur[v], step, last[v], x[v] < wd[u0 + v]);
             }
 #pragma unroll
             for (int v = 0; v < C; ++v) {
@@ -405,7 +403,7 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
 
     {
         // Words of every strip the group holds in LDS by place, and the
-        // strip-relative row pointers of rows 0..HB (rows past the strip: n).
+        // strip-relative row pointers of rows 0..HB (row_place).
         const bool fits = valid && !special;
         LdsWord* A = reinterpret_cast<LdsWord*>(slice) + gbase * E;
         LdsWord* B = A + kWave * E;
@@ -419,8 +417,8 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
             pos[u] = p;
             if (u < umax && fits && p < n) A[p] = wd[u];
         }
-        if (q < HB) rtab[q] = q < nr ? myrp - s0 : n;
-        if (q == 0) rtab[HB] = n;
+        if (q < HB) rtab[q] = row_place(fits, q, nr, myrp - s0, n);
+        if (q == 0) rtab[HB] = row_place(fits, HB, nr, 0, n);
         wave_lds_sync();
         // Rows must ascend (non-strictly) by column for the merge: an entry
         // and the next one of the strip, when they share the RowInStrip field

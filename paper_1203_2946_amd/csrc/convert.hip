@@ -241,6 +241,168 @@ __device__ inline void merge_runs_regs(LdsWord* A, LdsWord* B, const LdsInt* rt,
 // 64-bit words a search may read past the last wave's slice of kWave*E.
 constexpr int merge_pad(int E) { return kWave * E / 2; }
 
+// Unsorted rows, bucketed by column (see from_csr_tall_kernel): most keys of a
+// bucket, beyond which the strip goes through a bitonic network.
+constexpr int kBucketMax = 64;
+
+// Places (pos) in the sorted strip of the n words of a strip with unsorted rows
+// that a wave of the group kernel holds, slot u of lane q entry q + kWave*u: the
+// bucketing of from_csr_tall_kernel in the wave's LDS slice (A, B: kWave*E words
+// each), where A takes the words by bucket and B the buckets' starts and the
+// words' places in the strip, which order equal words.  Returns false, pos
+// unchanged, if a bucket is too full.  Listed, as they are below kBucketHeight, such
+// strips go through the list kernel's bitonic networks: 6*10^6 entries in strips of
+// 430 to 448, height 16, 292 us against 60 to 82 here.
+typedef __attribute__((address_space(3))) uint16_t LdsHalf;
+template <int E>
+__device__ inline bool bucket_places(LdsWord* A, LdsWord* B, const uint32_t (&wd)[E], int (&pos)[E], int n, int bits,
+                                     int lane) {
+    constexpr int NB = kWave * E / 4, PER = NB / kWave;
+    static_assert(NB + 1 + kWave * E / 2 <= kWave * E && PER * kWave == NB, "starts and places fit B");
+    LdsHalf* const place = reinterpret_cast<LdsHalf*>(B + kWave * E / 2);
+    int cmin = INT_MAX, cmax = -1;
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (lane + kWave * u < n) {
+            cmin = min(cmin, static_cast<int>(wd[u] >> bits));
+            cmax = max(cmax, static_cast<int>(wd[u] >> bits));
+        }
+    }
+    cmin = -wave_max(-cmin);
+    cmax = wave_max(cmax);
+    int nbk = 1;
+    while (nbk < NB && nbk * 4 < n) nbk <<= 1;
+    const uint64_t scale = (static_cast<uint64_t>(nbk) << 32) / (static_cast<uint64_t>(cmax - cmin) + 1u);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) B[lane * PER + k] = 0u;
+    wave_lds_sync();
+    uint32_t bs[E];  // bucket << 16 | slot in bucket
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        bs[u] = 0u;
+        if (lane + kWave * u < n) {
+            const uint32_t c = (wd[u] >> bits) - static_cast<uint32_t>(cmin);
+            const uint32_t bk = static_cast<uint32_t>((static_cast<uint64_t>(c) * scale) >> 32);
+            bs[u] = (bk << 16) | __hip_atomic_fetch_add(B + bk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    wave_lds_sync();
+    int cnt[PER], sum = 0, most = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        cnt[k] = static_cast<int>(B[lane * PER + k]);
+        sum += cnt[k];
+        most = max(most, cnt[k]);
+    }
+    if (wave_max(most) > kBucketMax) return false;
+    int run = sum;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int t = __shfl_up(run, off);
+        if (lane >= off) run += t;
+    }
+    run -= sum;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        B[lane * PER + k] = static_cast<uint32_t>(run);
+        run += cnt[k];
+    }
+    if (lane == kWave - 1) B[NB] = static_cast<uint32_t>(run);
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        const int i = lane + kWave * u;
+        if (i < n) {
+            const int at = static_cast<int>(B[bs[u] >> 16] + (bs[u] & 0xffffu));
+            A[at] = wd[u];
+            place[at] = static_cast<uint16_t>(i);
+        }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        const int i = lane + kWave * u;
+        if (i < n) {
+            int p = static_cast<int>(B[bs[u] >> 16]);
+            const int end = static_cast<int>(B[(bs[u] >> 16) + 1]);
+            for (int k = p; k < end; ++k) p += A[k] < wd[u] || (A[k] == wd[u] && place[k] < i) ? 1 : 0;
+            pos[u] = p;
+        }
+    }
+    return true;
+}
+
+// From this height (next power of two) on, a strip with unsorted rows is bucketed by
+// the wave of the group kernel that holds it; lower ones go through the network.
+constexpr int kBucketHeight = 16;
+
+// Each entry and its value (read again) to its place.
+template <int E, typename ET>
+__device__ inline void scatter_strip(const uint32_t (&wd)[E], const int (&pos)[E], int umax, int n, int s0,
+                                     const ET* __restrict__ val_in, uint32_t* __restrict__ col_word,
+                                     ET* __restrict__ val_out, int lane) {
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        if (u >= umax) break;
+        const int i = lane + kWave * u;
+        if (i < n && static_cast<unsigned>(pos[u]) < static_cast<unsigned>(n)) {
+            col_word[s0 + pos[u]] = wd[u];
+            val_out[s0 + pos[u]] = val_in[s0 + i];
+        }
+    }
+}
+
+// A strip of at most kWave*E entries with unsorted rows, its words in registers
+// (slot u of lane l: entry l + kWave*u): with BUCKET by buckets of columns, else or
+// where they don't divide, by a bitonic network over (word, position) keys.
+template <int E, bool BUCKET, typename ET>
+__device__ inline void sort_unsorted(LdsKey* slice, const uint32_t (&wd)[E], int n, int s0, int bits,
+                                     const ET* __restrict__ val_in, uint32_t* __restrict__ col_word,
+                                     ET* __restrict__ val_out, int lane) {
+    wave_lds_sync();  // the slice's words are read above; buckets or keys overwrite them
+    if constexpr (BUCKET) {
+        LdsWord* A = reinterpret_cast<LdsWord*>(slice);
+        int pos[E];
+        if (bucket_places<E>(A, A + kWave * E, wd, pos, n, bits, lane)) {
+            scatter_strip<E, ET>(wd, pos, uniform((n + kWave - 1) / kWave), n, s0, val_in, col_word, val_out, lane);
+            return;
+        }
+        wave_lds_sync();
+    }
+    const int P = pow2_at_least(n);
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        const int i = lane + kWave * u;
+        if (i < n)
+            slice[i] = (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
+        else if (i < P)
+            slice[i] = ~0ull;
+    }
+    wave_lds_sync();
+    bitonic_sort(slice, P, 0, lane, kWave, [] { wave_lds_sync(); });
+    for (int i = lane; i < n; i += kWave) {
+        const uint64_t kk = slice[i];
+        col_word[s0 + i] = static_cast<uint32_t>(kk >> 32);
+        val_out[s0 + i] = val_in[s0 + static_cast<int>(static_cast<uint32_t>(kk))];
+    }
+}
+
+// sort_unsorted for the group kernel's wave, whose one strip's words lie in its
+// slice; out of line, and the last thing that wave does: its registers would spill
+// those of the kernel around it (Poisson(15) rows, fp64, height 12, 1.5*10^6 rows:
+// 174 -> 271 us).
+template <int E, typename ET>
+__device__ __attribute__((noinline)) void sort_held_strip(LdsKey* slice, int n, int s0, int bits,
+                                                          const ET* __restrict__ val_in,
+                                                          uint32_t* __restrict__ col_word, ET* __restrict__ val_out,
+                                                          int lane) {
+    const LdsWord* A = reinterpret_cast<const LdsWord*>(slice);
+    uint32_t wd[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) wd[u] = lane + kWave * u < n ? A[lane + kWave * u] : 0u;
+    sort_unsorted<E, true, ET>(slice, wd, n, s0, bits, val_in, col_word, val_out, lane);
+}
+
 // Sorted conversion of one strip of at most kWave*E entries by the whole wave,
 // words in registers (slot u of lane l: entry l + kWave*u), in its LDS slice
 // of kWave*E 64-bit words: rows sorted by column, a merge of the row runs
@@ -289,33 +451,9 @@ __device__ inline void sort_strip_mid(int strip, int rows, int height, int bits,
         const int row_max = wave_max(lane < sr.nr ? next_row - sr.myrp : 0);
         merge_runs_regs<HB, kWave, E, false>(A, B, rt, wd, pos, umax, true, n, lane, row_max, n,
                                                  [] { wave_lds_sync(); });
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            if (u >= umax) break;
-            const int i = lane + kWave * u;
-            if (i < n && static_cast<unsigned>(pos[u]) < static_cast<unsigned>(n)) {
-                col_word[sr.s0 + pos[u]] = wd[u];
-                val_out[sr.s0 + pos[u]] = val_in[sr.s0 + i];
-            }
-        }
+        scatter_strip<E, ET>(wd, pos, umax, n, sr.s0, val_in, col_word, val_out, lane);
     } else {
-        const int P = pow2_at_least(n);
-        wave_lds_sync();  // A is read above; the keys overwrite it
-#pragma unroll
-        for (int u = 0; u < E; ++u) {
-            const int i = lane + kWave * u;
-            if (i < n)
-                slice[i] = (static_cast<uint64_t>(wd[u]) << 32) | static_cast<uint32_t>(i);
-            else if (i < P)
-                slice[i] = ~0ull;
-        }
-        wave_lds_sync();
-        bitonic_sort(slice, P, 0, lane, kWave, [] { wave_lds_sync(); });
-        for (int i = lane; i < n; i += kWave) {
-            const uint64_t kk = slice[i];
-            col_word[sr.s0 + i] = static_cast<uint32_t>(kk >> 32);
-            val_out[sr.s0 + i] = val_in[sr.s0 + static_cast<int>(static_cast<uint32_t>(kk))];
-        }
+        sort_unsorted<E, false, ET>(slice, wd, n, sr.s0, bits, val_in, col_word, val_out, lane);
     }
     wave_lds_sync();
 }
@@ -436,9 +574,11 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
         }
         const bool gbad = (ballot(bad) & group_mask(gbase, G)) != 0;
         special = special || (valid && gbad);
+        // Uniform: the wave's one strip, sorted below from the words in A.
+        const bool held = G == kWave && HB >= kBucketHeight && gbad;
         constexpr int WCAP = kWave * E;  // what sort_strip_mid<HB, E> holds
         constexpr int INLINE = kInlineSortMax < WCAP ? kInlineSortMax : WCAP;
-        if (valid && special && q == 0 && n > INLINE) {
+        if (valid && special && !held && q == 0 && n > INLINE) {
             if (n <= kWaveSortCap)
                 ws_small[atomicAdd(&ws_count[0], 1)] = strip;
             else
@@ -448,8 +588,9 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
         const int next_row = __shfl_down(myrp, 1);
         const int row_end = q + 1 < nr ? next_row : s1;
         const int row_max = HB > 1 ? wave_max(go && q < nr ? row_end - myrp : 0) : 0;
-        merge_runs_regs<HB, G, E, true>(A, B, rtab, wd, pos, umax, go, n, q, row_max, umax * G,
-                                         [] { wave_lds_sync(); });
+        if (!held)
+            merge_runs_regs<HB, G, E, true>(A, B, rtab, wd, pos, umax, go, n, q, row_max, umax * G,
+                                             [] { wave_lds_sync(); });
         // Out from registers: each entry to its place in the sorted strip.
         // (Staging through LDS as the tall-strip kernel does was measured
         // slower here: 133 -> 137 us at height 2, 156 -> 164 us at height 4.)
@@ -462,7 +603,10 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
             }
         }
         wave_lds_sync();  // the wave's slice is reused below
-        uint64_t mids = ballot(valid && special && q == 0 && n <= INLINE);
+        if constexpr (G == kWave && HB >= kBucketHeight) {
+            if (held) sort_held_strip<E, ET>(slice, n, s0, bits, val_in, col_word, val_out, lane);
+        }
+        uint64_t mids = ballot(valid && special && !held && q == 0 && n <= INLINE);
         while (mids) {
             const int leader = __ffsll(static_cast<unsigned long long>(mids)) - 1;
             mids &= mids - 1;
@@ -519,7 +663,6 @@ __device__ inline void write_sorted_keys(const Key* K, const StripRows& sr, int 
 // RowInStrip, then CSR order), so duplicates need no special path.  A strip whose
 // largest bucket holds more than kBucketMax keys (columns bunched at a few values
 // far apart) is sorted by a bitonic network over the same keys instead.
-constexpr int kBucketMax = 64;
 constexpr int kTallSlots = 8;
 // From this height (next power of two) on, strips whose columns range over at
 // least kSpread times their entries take the bucketing pass too, as long as no

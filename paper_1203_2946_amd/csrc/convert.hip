@@ -664,14 +664,17 @@ __device__ inline void write_sorted_keys(const Key* K, const StripRows& sr, int 
 // largest bucket holds more than kBucketMax keys (columns bunched at a few values
 // far apart) is sorted by a bitonic network over the same keys instead.
 constexpr int kTallSlots = 8;
-// From this height (next power of two) on, strips whose columns range over at
-// least kSpread times their entries take the bucketing pass too, as long as no
-// bucket then holds more than kSpreadBucketMax: five levels of merging cost more
-// than it does (60 000 Poisson(15) rows, fp64, height 32: 23.9 us merged, 18.6
-// bucketed).  Clustered columns, counted in vain, pay about 10 % (27-point stencil
-// of 10^6 rows 270 -> 300 us with the line at 16), so the line lies above those.
-constexpr int kSpreadHeight = 32;
-constexpr int kSpread = 32;
+// Sorted rows from kBucketHeight (next power of two) on take the bucketing pass too,
+// as long as no bucket then holds more than kSpreadBucketMax: the levels of merging
+// cost more than it does.  At four levels every strip tries (40 000 strips, fp64,
+// merged/bucketed: band of 81, height 16, 288/242 us; band of 129, height 12, 326/261;
+// Poisson(30) rows, height 16, 190/161; 3000 strips of Poisson(48) rows, height 12,
+// 28.8/22.6), at five only those whose columns range over at least kSpread times
+// their entries (60 000 Poisson(15) rows, height 32: 23.9/18.6), since clustered
+// columns, counted in vain or in full buckets, pay for it (40 000 strips, height 24,
+// 27-point stencil 270/302, band of 41 255/282).
+template <int HB>
+constexpr int kSpread = HB > kBucketHeight ? 32 : 0;
 constexpr int kSpreadBucketMax = 16;
 
 template <int HB, int NT, typename ET>
@@ -744,7 +747,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
     }
     bad = __syncthreads_or(bad);
     int cmin = INT_MAX, cmax = -1;
-    if (bad || HB >= kSpreadHeight) {  // uniform
+    if (!bad && HB >= kBucketHeight) {  // uniform
+        // The rows ascend: their first and last words, in every wave by itself.
+        const int r0 = lane < sr.nr ? start[lane] : 0, r1 = lane < sr.nr ? start[lane + 1] : 0;
+        if (r0 < r1) {
+            cmin = static_cast<int>(A[r0] >> bits);
+            cmax = static_cast<int>(A[r1 - 1] >> bits);
+        }
+        cmin = -wave_max(-cmin);
+        cmax = wave_max(cmax);
+    }
+    if (bad) {
 #pragma unroll
         for (int u = 0; u < E; ++u) {
             if (tid + NT * u < n) {
@@ -765,7 +778,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
             cmax = max(cmax, red[1][w]);
         }
     }
-    const bool spread = HB >= kSpreadHeight && cmax - cmin >= kSpread * n;
+    const bool spread = HB >= kBucketHeight && cmax - cmin >= kSpread<HB> * n;
     int pos[E];
 #pragma unroll
     for (int u = 0; u < E; ++u) pos[u] = tid + NT * u;
@@ -773,6 +786,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6))) void fr
     if (!merge) {
         int nbk = 1;
         while (nbk < NBMAX && nbk * 4 < n) nbk <<= 1;
+        __syncthreads();  // the row table is read above; the counts overwrite it
         for (int b = tid; b < NBMAX; b += NT) start[b] = 0;
         __syncthreads();
         // bucket(c) = ((c - cmin) * scale) >> 32 with scale = floor(2^32 nbk /
@@ -1792,13 +1806,21 @@ constexpr double kTall128Mean = 450.0, kTall256Mean = 900.0, kTall512Mean = 1850
 // 625 strips 19.1/14.8, 625 27-point stencil strips, fp32, 22.5/17.0; 1875 strips
 // 23.9/25.1; 256 / 512 threads, 98 Poisson(40) strips 20.4/15.1).
 constexpr int kTallFew = 1024;
+// From kBucketHeight on, strips that are all resident at once as workgroups of 128
+// (12 on a CU) go that way from a lower mean on: their latency counts, not their
+// issue (group kernel / one workgroup each: 2500 strips of Poisson(15) rows, fp64,
+// height 24, 23.0/18.8 us; 543 strips of one row of 368 and 31 of 2, height 32,
+// 21.8/15.0; but 3750 strips, band of 41, height 16, 24.4/25.7).
+constexpr int kTallResident = 3072;
+constexpr double kTallMeanFew = 320.0;
 
 template <int HB, typename ET>
 hipError_t from_csr_hb(const Conv& cv, const int* row_ptr, const int* col_ind, const void* val_in,
                        int* strip_ptr, uint32_t* col_word, void* val_out, void* workspace, hipStream_t stream) {
     const double mean = static_cast<double>(cv.nnz) / cv.strips;
-    if (mean >= kTall128Mean && mean < kTallEnd) {
-        const bool few = cv.strips <= kTallFew;
+    const bool few = cv.strips <= kTallFew;
+    const double from = HB >= kBucketHeight && cv.strips <= kTallResident ? kTallMeanFew : kTall128Mean;
+    if (mean >= from && mean < kTallEnd) {
         if (mean < kTall256Mean && !few)
             return from_csr_tall<HB, 128, ET>(cv, row_ptr, col_ind, val_in, strip_ptr, col_word, val_out, workspace,
                                               stream);

@@ -24,11 +24,10 @@ inline size_t dtype_bytes(cmrs_dtype_t t) {
     return 0;
 }
 
-// Strips that one wave sorts in its LDS slice (sorted conversion), and the
-// largest strip a 512-thread workgroup merges or sorts in LDS; longer strips
-// are streamed or sorted in the global workspace.
+// The largest strip that one wave sorts in its LDS slice (sorted conversion); a
+// workgroup merges up to that many entries per wave in LDS, and longer strips are
+// streamed or sorted in the global workspace.
 constexpr int kWaveSortCap = 1024;
-constexpr int kBlockSortCap = 8192;
 
 struct FromCsrWorkspaceLayout {
     size_t small_off;   // int32 counts at offset 0 (short / long list), short-strip list at small_off

@@ -47,10 +47,9 @@ namespace cmrs {
 
 constexpr int kConvWaves = 4;
 constexpr int kConvThreads = kConvWaves * kWave;
-constexpr int kBlockSortThreads = 512;
-// Workgroups of the listed-strip sort: its LDS and registers allow two per
-// CU, 256 CUs.
-constexpr int kBlockSortGrid = 512;
+// Threads of the listed-strip sort that are resident: its LDS and registers allow
+// 1024 per CU, 256 CUs.
+constexpr int kListThreads = 1024 * 256;
 
 __global__ void set_ints_kernel(int32_t* p, int32_t n, int32_t v) {
     if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < n) p[threadIdx.x] = v;
@@ -407,8 +406,10 @@ __device__ __attribute__((noinline)) void sort_held_strip(LdsKey* slice, int n, 
 // words in registers (slot u of lane l: entry l + kWave*u), in its LDS slice
 // of kWave*E 64-bit words: rows sorted by column, a merge of the row runs
 // (merge_runs_regs), then each entry and its value (read again) to its place;
-// otherwise a bitonic network over (word, position) keys.
-template <int HB, int E, typename ET>
+// otherwise a bitonic network over (word, position) keys.  KERNEL tells the callers
+// apart: with a copy of its own, each list kernel has it inlined (a call there costs
+// 7 us), while the group kernels share one out of line.
+template <int HB, int E, int KERNEL, typename ET>
 __device__ inline void sort_strip_mid(int strip, int rows, int height, int bits, const int* __restrict__ row_ptr,
                                       const int* __restrict__ col_ind, const ET* __restrict__ val_in,
                                       uint32_t* __restrict__ col_word, ET* __restrict__ val_out, LdsKey* slice,
@@ -610,8 +611,8 @@ __global__ __launch_bounds__(kConvThreads) __attribute__((amdgpu_waves_per_eu(8)
         while (mids) {
             const int leader = __ffsll(static_cast<unsigned long long>(mids)) - 1;
             mids &= mids - 1;
-            sort_strip_mid<HB, E, ET>(strip0 + leader / G, rows, height, bits, row_ptr, col_ind, val_in, col_word,
-                                      val_out, slice, (LdsInt*)rowtab[wave], lane);
+            sort_strip_mid<HB, E, 0, ET>(strip0 + leader / G, rows, height, bits, row_ptr, col_ind, val_in, col_word,
+                                         val_out, slice, (LdsInt*)rowtab[wave], lane);
         }
     }
 }
@@ -1502,12 +1503,14 @@ __device__ inline bool merge_strip_block(const StripRows& sr, int n, int row_max
 }
 
 // merge_strip_block for a strip of any length, keys in the strip's slice G
-// (2 n of them) of the workspace, C entries of a thread searched together.
+// (2 n of them) of the workspace, C entries of a thread searched together (four /
+// eight: 150 strips of eight rows of 1500 and 24 of 3, fp64, 183/157 us; of three
+// rows of 4000, 159/144).
 template <int HB, int NT, typename ET>
 __device__ inline bool merge_strip_global(const StripRows& sr, int n, int bits, const int* __restrict__ col_ind,
                                           const ET* __restrict__ val_in, uint32_t* __restrict__ col_word,
                                           ET* __restrict__ val_out, uint64_t* G, const int* rt, int tid) {
-    constexpr int C = 4;
+    constexpr int C = 8;
     const uint64_t rmask = (1ull << bits) - 1ull;
     const int n64 = (n + kWave - 1) / kWave * kWave;  // whole waves: the row lookup's cross-lane reads see all lanes
     for (int i = tid; i < n64; i += NT) {
@@ -1622,21 +1625,20 @@ __device__ inline int strip_row_ptr(int strip, int rows, int height, const int* 
 // their short ones last: skewed 2*10^6 rows, fp32, height 16, 154 us against 127;
 // short ones by a counter too: 129 us, and slower at heights 2 to 8.)  One long
 // row among short ones is streamed, other strips are merged in LDS while they fit
-// (kBlockSortCap words twice), in the workspace beyond that, and strips with
+// (CAP words twice), in the workspace beyond that, and strips with
 // unsorted rows go through a bitonic network afterwards.  A strip costs a chain
 // of dependent global loads (list entry, row pointers, then entries); the next
 // strip's list entry and row pointers are loaded while the current one is sorted.
-template <int HB, typename ET>
-__global__ __launch_bounds__(kBlockSortThreads) __attribute__((amdgpu_waves_per_eu(4))) void sort_lists_kernel(
+template <int HB, int NT, typename ET>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void sort_lists_kernel(
     int rows, int height, int bits, const int* __restrict__ row_ptr, const int* __restrict__ col_ind,
     const ET* __restrict__ val_in, uint32_t* __restrict__ col_word, ET* __restrict__ val_out,
     int* __restrict__ ws_count, const int* __restrict__ ws_small, const int* __restrict__ ws_big,
     uint64_t* __restrict__ gkeys) {
-    constexpr int NT = kBlockSortThreads, E = kBlockSortCap / NT;
-    constexpr int NWS = kBlockSortCap / kWaveSortCap;
-    static_assert(NWS == NT / kWave && 3 * kLightCap <= 2 * kBlockSortCap, "slices and light lists fit");
+    constexpr int E = kWaveSortCap / kWave, CAP = NT * E, NWS = NT / kWave;
+    static_assert(3 * kLightCap <= 2 * CAP, "light lists fit");
     // Eight bytes in front: a clamped search reads one word before the first.
-    __shared__ __align__(16) uint64_t lds[2 + kBlockSortCap + merge_pad(kWaveSortCap / kWave)];
+    __shared__ __align__(16) uint64_t lds[2 + CAP + merge_pad(E)];
     __shared__ int rt[HB + 1];
     __shared__ int taken[2];
     __shared__ int wrt[NWS][HB + 1];
@@ -1646,9 +1648,8 @@ __global__ __launch_bounds__(kBlockSortThreads) __attribute__((amdgpu_waves_per_
     const int wave = uniform(tid / kWave);
     const int scount = ws_count[0], count = ws_count[1];
     for (int it = static_cast<int>(blockIdx.x) * NWS + wave; it < scount; it += static_cast<int>(gridDim.x) * NWS)
-        sort_strip_mid<HB, kWaveSortCap / kWave, ET>(ws_small[it], rows, height, bits, row_ptr, col_ind, val_in,
-                                                     col_word, val_out, (LdsKey*)skeys + wave * kWaveSortCap,
-                                                     (LdsInt*)wrt[wave], lane);
+        sort_strip_mid<HB, E, NT, ET>(ws_small[it], rows, height, bits, row_ptr, col_ind, val_in, col_word, val_out,
+                                      (LdsKey*)skeys + wave * kWaveSortCap, (LdsInt*)wrt[wave], lane);
     __syncthreads();  // the long strips use the slices
     int item = static_cast<int>(gridDim.x - 1 - blockIdx.x);
     if (item < count) {
@@ -1683,7 +1684,9 @@ __global__ __launch_bounds__(kBlockSortThreads) __attribute__((amdgpu_waves_per_
             const uint64_t heavy = ballot(lane < HB && !light);
             uint64_t* const G = gkeys + 2 * static_cast<size_t>(sr.s0);
             bool bad;
-            if (__popcll(heavy) <= kHeavyMax && m <= kLightCap) {
+            // Two long rows of a low strip that fits: a level or two of merging cost less.
+            const int stream = NT == 1024 && HB <= 4 && n <= CAP ? 1 : kHeavyMax;
+            if (__popcll(heavy) <= stream && m <= kLightCap) {
                 uint32_t* LW = reinterpret_cast<uint32_t*>(skeys);
                 bad = __syncthreads_or(stream_strip<HB, NT, ET>(sr, rows_of, heavy, m, rls, bits, col_ind, val_in,
                                                                 col_word, val_out, LW, LW + kLightCap,
@@ -1691,17 +1694,17 @@ __global__ __launch_bounds__(kBlockSortThreads) __attribute__((amdgpu_waves_per_
             } else {
                 if (wave == 0 && lane <= HB) rt[lane] = lane < HB ? rows_of.lo : n;
                 __syncthreads();
-                if (n <= kBlockSortCap) {
-                    LdsWord* A = (LdsWord*)reinterpret_cast<uint32_t*>(skeys);
+                LdsWord* A = (LdsWord*)reinterpret_cast<uint32_t*>(skeys);
+                if (n <= CAP) {
                     bad = merge_strip_block<HB, NT, E, ET>(sr, n, wave_max(rows_of.len), bits, col_ind, val_in,
-                                                           col_word, val_out, A, A + kBlockSortCap, (LdsInt*)rt, tid);
+                                                           col_word, val_out, A, A + CAP, (LdsInt*)rt, tid);
                 } else {
                     bad = merge_strip_global<HB, NT, ET>(sr, n, bits, col_ind, val_in, col_word, val_out, G, rt, tid);
                 }
             }
             if (bad) {
                 __syncthreads();
-                bitonic_strip<HB, NT, kBlockSortCap, ET>(sr, n, bits, col_ind, val_in, col_word, val_out,
+                bitonic_strip<HB, NT, CAP, ET>(sr, n, bits, col_ind, val_in, col_word, val_out,
                                                          (LdsKey*)skeys, G, tid);
             }
             __syncthreads();  // the next item reuses skeys and rt
@@ -1730,23 +1733,48 @@ __global__ void validate_csr_kernel(int rows, int cols, int nnz, const int* __re
 
 namespace {
 
+// From this mean on every strip is listed.
+constexpr double kTallEnd = 3800.0;
+
 inline size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 
 struct Conv {
     int rows, strips, height, bits, nnz;
 };
 
-// Both lists of strips the first kernel could not sort (sort_lists_kernel):
-// two workgroups per CU, or fewer when the lists cannot be that long.
+// Both lists of strips the first kernel could not sort (sort_lists_kernel), by as
+// many workgroups as are resident, or fewer when the lists cannot be that long.
+// Workgroups of 512 threads, two on a CU, suit a few long strips among short ones and
+// strips of up to half an LDS.  Where every strip is listed, 1024 threads merge in LDS
+// what 512 take to the workspace (750 strips of 8000 in four rows, 512 / 1024 threads,
+// 183/113 us; 428 of 14 000 205/116), and while each has a CU to itself
+// they are faster below that too (31 strips of 8000 in four rows 65/33, 41 of 6000
+// with unsorted rows 108/89; but 1333 strips of 4500 with one long row, height 4,
+// 112/157).  Longer strips fit neither (300 strips of 20 000 in sixteen rows 380/438).
+constexpr double kWideLists = 7000.0, kWideListsEnd = 15000.0;
+constexpr int kWideListsFew = 256;
+template <int HB, int NT, typename ET>
+void launch_sort_lists_nt(const Conv& cv, const FromCsrWorkspaceLayout& L, const int* row_ptr, const int* col_ind,
+                          const ET* vin, uint32_t* col_word, ET* vout, int* ws_count, const int* ws_small,
+                          const int* ws_big, uint64_t* gkeys, hipStream_t stream) {
+    constexpr size_t NW = NT / kWave;
+    const size_t want = std::max<size_t>(L.big_cap, (L.small_cap + NW - 1) / NW);
+    const int g = static_cast<int>(std::max<size_t>(1, std::min<size_t>(want, kListThreads / NT)));
+    hipLaunchKernelGGL((sort_lists_kernel<HB, NT, ET>), dim3(g), dim3(NT), 0, stream, cv.rows, cv.height, cv.bits,
+                       row_ptr, col_ind, vin, col_word, vout, ws_count, ws_small, ws_big, gkeys);
+}
+
 template <int HB, typename ET>
 void launch_sort_lists(const Conv& cv, const FromCsrWorkspaceLayout& L, const int* row_ptr, const int* col_ind,
                        const ET* vin, uint32_t* col_word, ET* vout, int* ws_count, const int* ws_small,
                        const int* ws_big, uint64_t* gkeys, hipStream_t stream) {
-    constexpr size_t NW = kBlockSortCap / kWaveSortCap;
-    const size_t want = std::max<size_t>(L.big_cap, (L.small_cap + NW - 1) / NW);
-    const int g = static_cast<int>(std::max<size_t>(1, std::min<size_t>(want, kBlockSortGrid)));
-    hipLaunchKernelGGL((sort_lists_kernel<HB, ET>), dim3(g), dim3(kBlockSortThreads), 0, stream, cv.rows,
-                       cv.height, cv.bits, row_ptr, col_ind, vin, col_word, vout, ws_count, ws_small, ws_big, gkeys);
+    const double mean = static_cast<double>(cv.nnz) / cv.strips;
+    if (mean >= (cv.strips <= kWideListsFew ? kTallEnd : kWideLists) && mean < kWideListsEnd)
+        launch_sort_lists_nt<HB, 1024, ET>(cv, L, row_ptr, col_ind, vin, col_word, vout, ws_count, ws_small, ws_big,
+                                           gkeys, stream);
+    else
+        launch_sort_lists_nt<HB, 512, ET>(cv, L, row_ptr, col_ind, vin, col_word, vout, ws_count, ws_small, ws_big,
+                                          gkeys, stream);
 }
 
 template <int G, int E, int HB, typename ET>
@@ -1800,7 +1828,7 @@ hipError_t from_csr_tall(const Conv& cv, const int* row_ptr, const int* col_ind,
 // (512 entries) and is faster: means of 384 to 432 entries 149/74/200 us against
 // 185/112/248 (band of 81, fp32, height 8; band of 21, fp64, height 32; 27-point
 // stencil, fp64, height 16).
-constexpr double kTall128Mean = 450.0, kTall256Mean = 900.0, kTall512Mean = 1850.0, kTallEnd = 3800.0;
+constexpr double kTall128Mean = 450.0, kTall256Mean = 900.0, kTall512Mean = 1850.0;
 // Up to four strips per CU, where a strip's latency is the kernel's time, take twice
 // the threads (128 / 256 threads, height 32: 98 Poisson(15) strips, fp64, 18.7/13.9 us,
 // 625 strips 19.1/14.8, 625 27-point stencil strips, fp32, 22.5/17.0; 1875 strips

@@ -858,8 +858,10 @@ __device__ inline void spmm_tile_nv(const SpmmMat& m, int s0, int s1, AT* buf, i
 // overlap the current one's work as in the batched kernel.  One or two
 // right-hand sides: one pass per wave through spmm_pass_small, measured
 // faster there as a single launch (the batched kernel runs those buckets
-// through the pipelined loop too, where that was faster).
-template <int HB, int RB, typename VT, typename XT, typename AT>
+// through the pipelined loop too, where that was faster); NT as kNtLanesLog says, a
+// kernel each (with both kinds of loads in one, bf16 went from 64 to 65 registers
+// and from 8 to 7 waves per SIMD: 2*10^6 rows, band of 41, height 8, 96 -> 102 us).
+template <int HB, int RB, bool NT, typename VT, typename XT, typename AT>
 __global__ __launch_bounds__(kSpmmMaxWaves * kWave) void spmm_kernel(SpmmMat m, int strips, int passes) {
     extern __shared__ __align__(16) unsigned char spmm_lds[];
     AT* buf = reinterpret_cast<AT*>(spmm_lds);
@@ -877,17 +879,11 @@ __global__ __launch_bounds__(kSpmmMaxWaves * kWave) void spmm_kernel(SpmmMat m, 
         for (int i = 0; i < HB * RB; ++i) buf[i * kWave + lane] = AT(0);
         if constexpr (spmm_blk_type<VT>()) {
             if (m.nnz >= kBlk) {
-                if (m.g_log > kNtLanesLog)
-                    spmm_pass_small_blk<true, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
-                else
-                    spmm_pass_small_blk<false, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
+                spmm_pass_small_blk<NT, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
                 return;
             }
         }
-        if (m.g_log > kNtLanesLog)
-            spmm_pass_small<true, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
-        else
-            spmm_pass_small<false, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
+        spmm_pass_small<NT, HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
     } else {
         spmm_tile_nv<HB, RB, VT, XT, AT>(m, static_cast<int>(sb), s1, buf, lane);
     }
@@ -1026,7 +1022,14 @@ void launch_spmm_hb_rb(const SpmmMat& m, int strips, int wpb, size_t lds, hipStr
     while (RB > 2 && passes < kSpmmMaxPassesPerWave && npass >= 2LL * passes * 8192) passes *= 2;
     const long long waves = (npass + passes - 1) / passes;
     const int grid = static_cast<int>((waves + wpb - 1) / wpb);
-    hipLaunchKernelGGL((spmm_kernel<HB, RB, VT, XT, AT>), dim3(grid), dim3(wpb * kWave), lds, stream, m, strips,
+    if constexpr (RB <= 2) {
+        if (m.g_log > kNtLanesLog) {
+            hipLaunchKernelGGL((spmm_kernel<HB, RB, true, VT, XT, AT>), dim3(grid), dim3(wpb * kWave), lds, stream, m,
+                               strips, passes);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((spmm_kernel<HB, RB, false, VT, XT, AT>), dim3(grid), dim3(wpb * kWave), lds, stream, m, strips,
                        passes);
 }
 

@@ -44,7 +44,7 @@ if ROOT not in sys.path:
 METRIC = "CMRS SpMV GB/s & % HBM roofline (FP64/FP32); learned-vs-exhaustive tune ratio"
 HBM_PEAK_GBS = 8000.0
 SCHEDULES = {
-    "group": ("auto", None),            # strip groups, non-temporal stream loads (library default)
+    "group": ("auto", None),            # strip groups (library default)
     "wave": ("lds", None),              # one wave per strip, LDS partials (Algorithm 1 as printed)
     "wave_nt": ("lds_nt", None),        # the same with non-temporal Val/word loads
     "colblock4": ("auto", 4),           # column-blocked, one launch, 4 blocks

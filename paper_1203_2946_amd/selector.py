@@ -145,7 +145,7 @@ class ClassRunner:
         if s == "colblock4":
             cmrs.spmv_colblock(M, self.plans[h], self.x, out=self.y, schedule="concurrent", workspace=self.ws[h])
         else:
-            cmrs.spmv(M, self.x, out=self.y, variant={"wave": "lds", "wave_nt": "lds_nt", "group": "group_nt"}[s])
+            cmrs.spmv(M, self.x, out=self.y, variant={"wave": "lds", "wave_nt": "lds_nt", "group": "auto"}[s])
 
     def time_classes(self, classes=None, reps: int = 5) -> np.ndarray:
         """Median time (ms) of each class, warm, HIP events on the stream."""

@@ -70,7 +70,7 @@ typedef enum {
 #define CMRS_MAX_INDEX 2147418112
 
 /* SpMV kernel variants (cmrs_spmv `variant`). */
-#define CMRS_SPMV_AUTO 0   /* library's choice for (height, dtype)                  */
+#define CMRS_SPMV_AUTO 0   /* GROUP or GROUP_NT, by mean strip length and dtype      */
 #define CMRS_SPMV_LDS 1    /* one wave64 per strip, per-lane partial sums in LDS     */
 #define CMRS_SPMV_REG 2    /* one wave64 per strip, per-lane partial sums in VGPRs   */
 #define CMRS_SPMV_LDS_NT 3 /* LDS, Val / word streams read with non-temporal loads   */
@@ -175,7 +175,8 @@ cmrs_status_t cmrs_to_csr(const cmrs_mat_t *A, int32_t *row_ptr_out, int32_t *co
  *   xy_dtype          R64F with R64F values (fp64 arithmetic), R32F with R32F
  *                     values (fp32 arithmetic), or R32F with R16BF values
  *                     (values widened to fp32, fp32 arithmetic).
- *   variant           CMRS_SPMV_* (AUTO picks per height and dtype).
+ *   variant           CMRS_SPMV_* (AUTO picks by height, mean strip length and
+ *                     dtype; the same bits as the variant it picks).
  * y is overwritten (Algorithm 1 assigns the row sums): rows without entries
  * get +0.0.  rows == 0 is a no-op.  Deterministic: the same inputs give the
  * same bits on every call.
@@ -237,7 +238,7 @@ cmrs_status_t cmrs_spmv_colblock(const cmrs_mat_t *A, const void *x, void *y, cm
  * long_len stored entries is "heavy": a plan cuts it into chunks of at most
  * chunk_len consecutive entries, chunk waves compute the chunks' row sums
  * (each as Algorithm 1 computes a strip) while all other strips run as
- * strip groups (CMRS_SPMV_GROUP_NT), and a second small launch adds each
+ * strip groups (CMRS_SPMV_GROUP or _NT as AUTO), and a second small launch adds each
  * split strip's chunk sums in chunk order and writes its rows.  y is
  * overwritten, the error bound of cmrs_spmv holds, results are
  * deterministic.
@@ -365,11 +366,12 @@ cmrs_status_t cmrs_spmm(const cmrs_mat_t *A, int32_t nrhs, const void *X, int32_
  * filled by cmrs_spmm_plan) and CMRS_OK without launching for zero tiles.
  */
 typedef struct {
-    int32_t tile_nnz;       /* stored entries per work tile (rounded to whole
-                               strip passes); 0 = by the batch's entries: 32768
-                               below 2^18, then about 3500 tiles of at least
-                               1024, from 5*10^7 on 4096 (and 32768 if `desc`
-                               holds only that many tiles)                     */
+    int32_t tile_nnz;       /* stored entries per work tile (rounded down to
+                               whole strip passes, at least one); 0 = by the
+                               batch's entries: 32768 below 2^18, then their
+                               3500th part but at least 1024, from 5*10^7 on
+                               4096 (and 32768 if `desc` holds only that many
+                               tiles)                                          */
     int32_t group;          /* entry slots per strip, a power of two; 0 = from
                                each matrix's mean strip length                 */
     int32_t blocks_per_cu;  /* resident 256-thread workgroups per compute unit;

@@ -77,6 +77,15 @@ hipError_t launch_to_csr(const cmrs_mat_t* A, int32_t* row_ptr, int32_t* col_ind
 // 64 47/48.  Column blocks: fp32 height 32 (32 lanes) 105/90, fp64 height 8 (8)
 // 185/150, height 32 (32) 122/124.  Split schedule: fp64 height 16 100/93, bf16
 // height 32 67/62.
+// Those are repeated calls.  With the caches full of other data that was read, cached
+// loads lose nowhere (1024 x 1024 5-point Laplacian, fp64, height 8, 29.5/21.0; skewed
+// rows, fp64, height 8, 124/114); full of another kernel's unwritten lines, they have
+// to write those back for the lines they allocate, which a non-temporal load does not,
+// and matrices that fit the last-level cache lose (after 1 GiB of writes: that
+// Laplacian 29.1/31.9, 27-point stencil of 10^6 rows, fp32, height 4, 66/80, Poisson(16)
+// rows, fp32, height 4, 149/159; but 1.2*10^7 rows of 5 292/229, and 4*10^6 of 27,
+// height 1, 418/338).  A call does not know what ran before it, so the line is drawn by
+// the repeated ones.
 constexpr bool stream_past_cache(int g, size_t value_bytes) { return g * (value_bytes > 4 ? value_bytes : 4) > 128; }
 template <typename VT>
 constexpr bool stream_past_cache(int g) {

@@ -63,7 +63,10 @@ __device__ inline T stream_load(const T* p) {
 // past it: 10^6 random rows of 30 entries, fp64, 32 and 64 lanes, 314/330 and
 // 309/326, fp32 194/203 and 188/199, bf16, 2 columns, 287/293 and 278/288;
 // but 8 and 16 lanes, 400 000 rows of 8, fp64 34/27 and 33/26, fp32 29/22 and
-// 28/22, bf16 34/21 and 30/21.
+// 28/22, bf16 34/21 and 30/21.  As for one column, cached loads lose where the caches
+// are full of another kernel's unwritten lines (27-point stencil of 10^6 rows, 2
+// columns, fp32, height 4, 63/87 after 1 GiB of writes; at most 1 % after 1 GiB of
+// reads, over 120 shapes 0.95 of the time).
 constexpr int kNtLanesLog = 4;
 
 template <int RB>
@@ -1129,10 +1132,16 @@ SpmmPlanShape spmm_plan_shape(int count, const cmrs_mat_t* mats, const int* nrhs
                               std::vector<SpmmTile>* tiles_out) {
     SpmmPlanShape sh{};
     // Entries per tile.  A batch of at least kRounds tiles of kTileMost entries for
-    // each of the chip's waves takes those (larger ones end unevenly, smaller ones
-    // start over too often); below that every wave gets one tile, of a size that
-    // leaves some waves over and no second round for a few tiles.  Below kTileSmall
-    // entries 32768.  (us at 6144 / 4096 / 2048 entries: 32 matrices of 129 M,
+    // each of kWaves waves (all of a chip of 256 CUs, 16 on each) takes those (larger
+    // ones end unevenly, smaller ones start over too often); below that as many tiles
+    // as 0.85 of the waves.  Both are aims: a tile is rounded down to whole passes of
+    // its matrix (at least one), so matrices whose passes hold hundreds of entries get
+    // up to twice the tiles, and plans with fewer waves (fewer workgroups asked for, or
+    // tall strips with many right-hand sides, whose partials leave room for less than
+    // four waves in a workgroup) take them in several rounds.  Below kTileSmall entries
+    // the size stays at the 32768 that all batches had, whose plan buffers callers may
+    // have sized; it is not the fastest there (206 400 entries in three matrices, fp64,
+    // 213 us, and 12 at 1024, which `tile_nnz` asks for).  (us at 6144 / 4096 / 2048 entries: 32 matrices of 129 M,
     // fp64 545/533/553, fp32 393/394/421; 8 of 17.8 M, fp64 99/112/120; 4 of 7.2 M,
     // fp32 60/44/34; 3 of 1.1 M, fp64 60/42/24 and 16 at 1024.  At 32768, with
     // non-temporal stream loads: 722, 487, 363, 274 and 338.)

@@ -29,12 +29,12 @@
 // (binary search) and moves to its place in the merged run.  Keys are
 // (word << 32 | position in strip), unique, so the result is the stable order.
 // Matrices of longer strips (a mean of 450 to 3800 entries) give each strip to a
-// workgroup, which merges the same way.  Strips that are longer than that, or
-// whose rows are not sorted, go to a list in the workspace: strips of up to 1024
+// workgroup, which merges the same way or sorts by buckets of columns.  Strips that
+// are longer than that, or short ones whose rows are not sorted, go to a list in the workspace: strips of up to 1024
 // entries are sorted by one wave (run merge, or a bitonic network for unsorted
-// rows); of longer ones, one long row among short ones is streamed against the
-// short rows' sorted words, others are merged by a workgroup in LDS up to 8192
-// entries, in the workspace beyond that, unsorted rows by a bitonic network.
+// rows); of longer ones, few long rows among short ones are streamed against the
+// short rows' sorted words, others are merged by a workgroup in LDS as far as that
+// holds them, in the workspace beyond, unsorted rows by a bitonic network.
 #include <limits.h>
 
 #include <type_traits>
@@ -651,8 +651,8 @@ __device__ inline void write_sorted_keys(const Key* K, const StripRows& sr, int 
 // 157 on 2^20 Poisson(16) rows, fp64, height 32; one wave per strip with 20
 // entries per lane had four: 249 us).  Strips like these went to the lists or,
 // bunched columns at height 16 and up, through the bitonic network: band of 129,
-// fp32, height 8/16/32 1068/3252/3313 -> 212/282/456 us; 27-point stencil, fp64,
-// height 32 640 -> 270 us; Poisson(48) rows, fp64, height 32 3840 -> 231 us.
+// fp32, height 8/16/32 1068/3252/3313 -> 212/221/426 us; 27-point stencil, fp64,
+// height 32 640 -> 271 us; Poisson(48) rows, fp64, height 32 3840 -> 210 us.
 //
 // Rows not sorted: one bucketing pass, whatever the height: entries fall into NB
 // buckets of about equal width over the strip's column range [cmin, cmax] (NB
@@ -1295,11 +1295,12 @@ __device__ inline void count_below(const uint32_t* S, const uint32_t (&w)[C], co
 }
 
 // Rows of at most kLightRow entries are light, the others heavy.  A listed strip
-// of at most kHeavyMax heavy rows and kLightCap entries in light ones (one long
-// row among short ones, as skewed matrices have them) is streamed.
+// of at most kHeavyMax heavy rows (kHeavyStaged where only the workspace could merge
+// it) and kLightCap entries in light ones (a long row or few among short ones, as
+// skewed matrices have them) is streamed.
 constexpr int kLightRow = 64;
 constexpr int kLightCap = 512;
-constexpr int kHeavyMax = 2;
+constexpr int kHeavyMax = 2, kHeavyStaged = 4;
 
 // The rows of a long strip, row x in lane x of every wave: its first entry in
 // the strip and its length (rows past the strip: n, 0).
@@ -1321,10 +1322,14 @@ __device__ inline RunTable run_table(const StripRows& sr, int n, int lane) {
 // same words for every lane: no bank conflicts, no dependent loads), and SL takes
 // the light words in order.  A heavy entry's place is its index in its row plus
 // its count of light words below (a binary search over SL) plus one over each
-// other heavy row in global memory; a light entry's is its rank plus, for each
-// heavy row, the first entry that has counted it (H).  A heavy row's entries are read in order and
-// leave in nearly that order, so nothing of it is held: the strip costs two
-// barriers and a few KiB of LDS, and two workgroups share a CU.  (With the whole
+// other heavy row; a light entry's is its rank plus, for each heavy row, the first
+// entry that has counted it (H).  A heavy row's entries are read in order and
+// leave in nearly that order, so nothing of it is held but, for the searches of
+// another heavy row, the strip's columns where they fit (staged: HC, by place);
+// otherwise those searches read global memory (150 strips of two rows of 4000 and
+// 30 of 3, fp64, global / staged 71/65 us, and three such rows 124/103; the merge in
+// the workspace takes 144 for those).  The strip costs few barriers, and two
+// workgroups share a CU.  (With the whole
 // strip's words in LDS, one workgroup of 1024 threads per CU, the listed strips of
 // the skewed 2*10^6-row workload, fp32, height 16, took 152 us at a quarter of the
 // VALU rate, 32 us a strip and workgroup, nearly all latency between barriers; now
@@ -1333,7 +1338,7 @@ template <int HB, int NT, typename ET>
 __device__ inline bool stream_strip(const StripRows& sr, const RunTable& rows_of, uint64_t heavy, int m, int rls,
                                     int bits, const int* __restrict__ col_ind, const ET* __restrict__ val_in,
                                     uint32_t* __restrict__ col_word, ET* __restrict__ val_out, uint32_t* LW,
-                                    uint32_t* SL, int* H, int tid, int lane) {
+                                    uint32_t* SL, int* H, int* HC, bool staged, int tid, int lane) {
     static_assert(NT >= kLightCap, "one light entry per thread");
     constexpr int C = 4;  // entries of a heavy row searched together
     const uint32_t rmask = (1u << bits) - 1u;
@@ -1344,6 +1349,18 @@ __device__ inline bool stream_strip(const StripRows& sr, const RunTable& rows_of
     ET v = ET(0);
     int pos = 0;
     const bool mine = tid < m;
+    if (staged) {
+        const int n = sr.s1 - sr.s0;
+        for (int i = tid; i < n; i += NT) HC[i] = col[i];
+        __syncthreads();
+        // Unsorted rows show here for little.
+        for (uint64_t hm = heavy; hm; hm &= hm - 1) {  // uniform
+            const int r = __ffsll(static_cast<unsigned long long>(hm)) - 1;
+            const int lo = __shfl(rows_of.lo, r), len = __shfl(rows_of.len, r);
+            for (int i = tid; i + 1 < len; i += NT) bad = bad || HC[lo + i + 1] < HC[lo + i];
+        }
+        if (__syncthreads_or(bad)) return true;
+    }
     {
         const int r = row_in_strip<HB>(lane < HB ? rls : INT_MAX, tid, 0);
         const int lo = __shfl(rows_of.lo, r), first = __shfl(rls, r);
@@ -1413,20 +1430,26 @@ __device__ inline bool stream_strip(const StripRows& sr, const RunTable& rows_of
             for (uint64_t om = heavy & ~(1ull << r); om; om &= om - 1) {  // uniform
                 const int x = __ffsll(static_cast<unsigned long long>(om)) - 1;
                 const int xlo = __shfl(rows_of.lo, x), xlen = __shfl(rows_of.len, x);
-                // Entries of the other heavy row, in global memory, that sort
-                // before this one: columns below, or equal in an earlier row.
+                // Entries of the other heavy row that sort before this one:
+                // columns below, or equal in an earlier row.
                 int below[C];
 #pragma unroll
                 for (int k = 0; k < C; ++k) below[k] = 0;
+                const auto search = [&](const int* row) {
 #pragma unroll 1
-                for (int step = 1 << (31 - __clz(xlen)); step > 0; step >>= 1) {
-                    int y[C];
+                    for (int step = 1 << (31 - __clz(xlen)); step > 0; step >>= 1) {
+                        int y[C];
 #pragma unroll
-                    for (int k = 0; k < C; ++k) y[k] = col[xlo + min(below[k] + step, xlen) - 1];
+                        for (int k = 0; k < C; ++k) y[k] = row[min(below[k] + step, xlen) - 1];
 #pragma unroll
-                    for (int k = 0; k < C; ++k)
-                        if (below[k] + step <= xlen && (y[k] < c[k] || (x < r && y[k] == c[k]))) below[k] += step;
-                }
+                        for (int k = 0; k < C; ++k)
+                            if (below[k] + step <= xlen && (y[k] < c[k] || (x < r && y[k] == c[k]))) below[k] += step;
+                    }
+                };
+                if (staged)
+                    search(HC + xlo);
+                else
+                    search(col + xlo);
 #pragma unroll
                 for (int k = 0; k < C; ++k) cnt[k] += below[k];
             }
@@ -1623,8 +1646,8 @@ __device__ inline int strip_row_ptr(int strip, int rows, int height, const int* 
 // zero at launch), so strips of very different lengths spread evenly.  (The other
 // way round, the workgroups that had sorted long strips until late started on
 // their short ones last: skewed 2*10^6 rows, fp32, height 16, 154 us against 127;
-// short ones by a counter too: 129 us, and slower at heights 2 to 8.)  One long
-// row among short ones is streamed, other strips are merged in LDS while they fit
+// short ones by a counter too: 129 us, and slower at heights 2 to 8.)  Few long
+// rows among short ones are streamed, other strips are merged in LDS while they fit
 // (CAP words twice), in the workspace beyond that, and strips with
 // unsorted rows go through a bitonic network afterwards.  A strip costs a chain
 // of dependent global loads (list entry, row pointers, then entries); the next
@@ -1636,9 +1659,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void so
     int* __restrict__ ws_count, const int* __restrict__ ws_small, const int* __restrict__ ws_big,
     uint64_t* __restrict__ gkeys) {
     constexpr int E = kWaveSortCap / kWave, CAP = NT * E, NWS = NT / kWave;
-    static_assert(3 * kLightCap <= 2 * CAP, "light lists fit");
+    // Behind the slices: what a search of the last one may read, and the light lists
+    // of a streamed strip whose STAGE columns fill the rest.
+    constexpr int PAD = std::max(merge_pad(E), 3 * kLightCap / 2), STAGE = 2 * CAP;
     // Eight bytes in front: a clamped search reads one word before the first.
-    __shared__ __align__(16) uint64_t lds[2 + CAP + merge_pad(E)];
+    __shared__ __align__(16) uint64_t lds[2 + CAP + PAD];
     __shared__ int rt[HB + 1];
     __shared__ int taken[2];
     __shared__ int wrt[NWS][HB + 1];
@@ -1684,13 +1709,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void so
             const uint64_t heavy = ballot(lane < HB && !light);
             uint64_t* const G = gkeys + 2 * static_cast<size_t>(sr.s0);
             bool bad;
-            // Two long rows of a low strip that fits: a level or two of merging cost less.
-            const int stream = NT == 1024 && HB <= 4 && n <= CAP ? 1 : kHeavyMax;
-            if (__popcll(heavy) <= stream && m <= kLightCap) {
+            // Streamed: up to kHeavyMax long rows, and up to kHeavyStaged where their
+            // columns fit LDS but a merge would not.  (With two long rows of a low
+            // strip, a level or two of merging costs 1024 threads less.)
+            const int nheavy = __popcll(heavy);
+            const bool staged = HB > 1 && nheavy > 1 && n <= STAGE;
+            const int most = n <= CAP ? (NT == 1024 && HB <= 4 ? 1 : kHeavyMax) : (staged ? kHeavyStaged : kHeavyMax);
+            if (nheavy <= most && m <= kLightCap) {
                 uint32_t* LW = reinterpret_cast<uint32_t*>(skeys);
-                bad = __syncthreads_or(stream_strip<HB, NT, ET>(sr, rows_of, heavy, m, rls, bits, col_ind, val_in,
-                                                                col_word, val_out, LW, LW + kLightCap,
-                                                                reinterpret_cast<int*>(LW + 2 * kLightCap), tid, lane));
+                bad = __syncthreads_or(stream_strip<HB, NT, ET>(
+                    sr, rows_of, heavy, m, rls, bits, col_ind, val_in, col_word, val_out, LW, LW + kLightCap,
+                    reinterpret_cast<int*>(LW + 2 * kLightCap), reinterpret_cast<int*>(LW + 3 * kLightCap), staged, tid,
+                    lane));
             } else {
                 if (wave == 0 && lane <= HB) rt[lane] = lane < HB ? rows_of.lo : n;
                 __syncthreads();
